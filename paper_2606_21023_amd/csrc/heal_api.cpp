@@ -67,14 +67,6 @@ heal_status_t for_each_part(int64_t batch, int64_t M, int64_t N, F launch)
     return HEAL_OK;
 }
 
-int select_instance(int64_t M, int64_t N)
-{
-    (void)N;
-    if (M <= 64) return HEAL_INSTANCE_SKINNY;
-    if (M * N <= (int64_t)2048 * 2048) return HEAL_INSTANCE_MEDIUM;
-    return HEAL_INSTANCE_LARGE;
-}
-
 // Validate a strided-batched call; returns HEAL_OK if it may proceed.
 heal_status_t validate(int64_t M, int64_t N, int64_t K, const float *A, int64_t lda,
                        int64_t strideA, const float *B, int64_t ldb, int64_t strideB, int trans_b,
@@ -134,8 +126,7 @@ heal_status_t run_gemm(int instance, int64_t M, int64_t N, int64_t K, float alph
         a.A = A ? A + b0 * strideA + m0 * lda : A;   // null only when K == 0
         a.B = B ? B + b0 * strideB + (trans_b ? n0 * ldb : n0) : B;
         a.C = C + b0 * strideC + m0 * ldc + n0;
-        const int inst = instance == HEAL_INSTANCE_AUTO ? select_instance(mn, nn) : instance;
-        return heal::launch_gemm(inst, a, trans_b != 0, use_alpha, stream);
+        return heal::launch_gemm(instance, a, trans_b != 0, use_alpha, stream);
     });
 }
 
@@ -185,6 +176,14 @@ heal_status_t run_packed(int op, int instance, int64_t M, int64_t N, int64_t K, 
 }
 
 }  // namespace
+
+int heal::select_instance(int64_t M, int64_t N)
+{
+    (void)N;
+    if (M <= 64) return HEAL_INSTANCE_SKINNY;
+    if (M * N <= (int64_t)2048 * 2048) return HEAL_INSTANCE_MEDIUM;
+    return HEAL_INSTANCE_LARGE;
+}
 
 extern "C" {
 
@@ -246,7 +245,7 @@ heal_status_t heal_gemm_f32_instance(int instance, int64_t M, int64_t N, int64_t
                     strideC, batch, stream);
 }
 
-int heal_gemm_select_instance(int64_t M, int64_t N) { return select_instance(M, N); }
+int heal_gemm_select_instance(int64_t M, int64_t N) { return heal::select_instance(M, N); }
 
 // ---- FP16 forms, pre-split operand, INT16 scores ----------------------------
 

@@ -1,0 +1,700 @@
+// The direct-B GEMM kernel for gfx950 (MI355X): products whose output gives a
+// chip of 256 CUs too few large tiles, i.e. most products of more than 64 rows
+// and less than about 2048 x 4096 elements, on operands of any alignment.
+//
+// All products of an FP32 A (HEAL Section 4, GEMM paragraph) run on it:
+// HEAL-Base, HEAL-Full and the pre-split bf16x3 product with their packed B,
+// and the bf16x3 product with B stored N x K or K x N.
+//
+// What bounds such a product is not the matrix cores but the time of one
+// stage on one CU: with 128 x 128 tiles a 256 x 4096 output occupies 64 of 256
+// CUs.  K cannot be split (each element's sum keeps one order), so the tiles
+// have to be small, and what a tile stages per 32 of K is then large against
+// its MFMAs: the CU's load path (64 bytes per clock), the LDS store path and
+// the conversions of A.  Hence:
+//   * each wave owns its columns: B goes from memory to its registers, in
+//     fragment order, with no LDS round trip and no sharing; B stored K x N is
+//     read as one to four adjacent columns per lane (block j of a wave takes
+//     every NB-th column from the j-th), so the 4 x 4 transposes of the staged
+//     kernels are not needed;
+//   * LW more waves do nothing but stage A: they load, convert and store it to
+//     a ring of three LDS stages, one stage ahead of the fragment reads;
+//   * the computing waves read the next chunk's fragments of A and split its B
+//     while the current chunk is multiplied (PIPE), and their B is in flight
+//     RC chunks ahead.
+// Measured (4096 x 4096 weight, us, tiled kernels -> this one): 256 rows
+// HEAL-Full 72.8 -> 25.6, HEAL-Base 43.4 -> 19.4, pre-split 92.1 -> 31.8, bf16x3
+// 84.2 -> 40.6 (K x N) and 87.5 -> 41.9 (N x K); 1024 rows 85.6 -> 74.5, 53.7 ->
+// 50.6, 104.4 -> 92.7, 110.2 -> 107.3, 113.7 -> 111.0.  At 256 rows HEAL-Full
+// takes 15.7 us with neither A nor B loaded, 23.1 without A's staging.
+//
+// Alignment: the hardware's 16-byte buffer accesses need dword alignment only,
+// so every 4-byte aligned row takes this path.  A quad across the end of a
+// row of K (or the lane's columns across the end of a row of B stored K x N)
+// is read up to three elements early, inside its row, and shifted.
+//
+// Reduction order: identical to every other instance (K in 32-deep chunks
+// ascending; per chunk the products in their fixed order into one FP32
+// accumulator; the B fragment as the MFMA's first source; the K tail
+// zero-filled), so results are bitwise equal to theirs.
+#include "heal.h"
+#include "heal_device.h"
+#include "heal_internal.h"
+
+namespace heal {
+
+namespace {
+
+constexpr uint32_t kOOB = 0x80000000u;  // buffer offset beyond every range: reads 0
+constexpr int kRsrcFlags = 0x00020000;  // raw buffer, 32-bit data format
+
+// Vector of four floats with the alignment of one: C rows need not be 16-byte
+// aligned (the hardware's 16-byte accesses need dword alignment only).
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+enum BSource : int {
+    B_PACKED = 0,  // fragment order: one 1 KiB block per 16 columns, 32-deep chunk and plane
+    B_ROWS = 1,    // FP32, stored N x K
+    B_COLS = 2,    // FP32, stored K x N
+};
+
+
+template <int OP>
+struct DirectOp {
+    static constexpr int AP = OP == OP_BASE ? 1 : 2;       // LDS planes of A
+    static constexpr int BP = OP == OP_PRESPLIT ? 2 : 1;   // packed planes of B
+    static constexpr bool BF16 = OP == OP_PRESPLIT || OP == OP_BF16X3;
+};
+
+template <bool BF16>
+__device__ __forceinline__ f32x4 mma(u32x4 b, u32x4 a, f32x4 c)
+{
+    if constexpr (BF16)
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b),
+                                                       __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, b),
+                                                      __builtin_bit_cast(f16x8, a), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, bytes, kRsrcFlags);
+}
+
+__device__ __forceinline__ u32x4 bload4(__amdgpu_buffer_rsrc_t r, uint32_t voff, int soff)
+{
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, soff, 0));
+}
+
+// V consecutive floats, V = 1, 2 or 4.
+template <int V>
+__device__ __forceinline__ void bload_v(__amdgpu_buffer_rsrc_t r, uint32_t voff, int soff, float *v)
+{
+    if constexpr (V == 4) {
+        const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, soff, 0));
+        v[0] = x.x;
+        v[1] = x.y;
+        v[2] = x.z;
+        v[3] = x.w;
+    } else if constexpr (V == 2) {
+        const f32x2 x = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, soff, 0));
+        v[0] = x.x;
+        v[1] = x.y;
+    } else {
+        v[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, soff, 0));
+    }
+}
+
+// kOOB for an index past the end, else 0: a lane's offset with it set lies
+// beyond the buffer.  Arithmetic, not a select, which becomes a branch around
+// the loads, after which every wait is for all of them.
+__device__ __forceinline__ uint32_t past_end(int i, int n)
+{
+    return (uint32_t)((n - 1 - i) >> 31) & kOOB;
+}
+
+// A quad read `back` elements early (0 to 3, so that it ends at the end of its
+// row): the elements that belong to it move to the front, zeros follow.
+__device__ __forceinline__ u32x4 shift_quad(u32x4 q, int back)
+{
+    u32x4 v = q;
+    if (back == 1) v = u32x4{q.y, q.z, q.w, 0u};
+    if (back == 2) v = u32x4{q.z, q.w, 0u, 0u};
+    if (back == 3) v = u32x4{q.w, 0u, 0u, 0u};
+    return v;
+}
+
+// LDS geometry of one plane of A: rows of BK 16-bit values, the 16-byte chunk
+// c of row r at c ^ swz(r), so that the 16 rows of a fragment read fall in
+// different bank groups.
+template <int BK>
+struct LdsA {
+    static constexpr int RP = 2 * BK;
+    static __device__ __forceinline__ int swz(int row)
+    {
+        return RP >= 256 ? row & 15 : RP == 128 ? (row >> 1) & 7 : (row >> 1) & 3;
+    }
+    static __device__ __forceinline__ int chunk_off(int row, int c)
+    {
+        return row * RP + ((c ^ swz(row)) << 4);
+    }
+    static __device__ __forceinline__ int quad_off(int row, int kq)
+    {
+        return row * RP + (((kq >> 1) ^ swz(row)) << 4) + ((kq & 1) << 3);
+    }
+};
+
+// MB, NB: 16-row and 16-column blocks per wave; WVM, WVN: waves along M and N;
+// KS: 32-deep chunks per stage; RC: chunks of B in flight per wave; LW: waves
+// that stage A; RA: their register sets; PIPE: fragments of A read a chunk
+// ahead (twice the registers); TAIL: K is not a multiple of the stage depth.
+template <int OP, int BS, int MB, int WVM, int NB, int WVN, int KS, int RC, int LW, int RA, bool PIPE, bool TAIL>
+__global__ void __launch_bounds__(64 * (WVM * WVN + LW), (WVM * WVN + LW) / 4)
+gemm_direct_kernel(DirectArgs p)
+{
+    using O = DirectOp<OP>;
+    constexpr int CW = WVM * WVN;                // waves that multiply
+    constexpr int NT = 64 * LW;                  // threads that stage A
+    constexpr int D = 3;                         // LDS stages
+    constexpr int T = RC > KS ? RC / KS : 1;     // stages per trip of the compute loop
+    static_assert(RC % KS == 0 || KS % RC == 0, "whole turns of the B ring per trip");
+    constexpr int BM = 16 * MB * WVM, BN = 16 * NB * WVN, BK = 32 * KS, KQ = BK / 4;
+    using L = LdsA<BK>;
+    constexpr int A_PLANE = BM * L::RP;
+    constexpr int STAGE = O::AP * A_PLANE;
+    constexpr int NA = BM * KQ / NT;             // A quads per thread and stage
+    static_assert(NA >= 1 && NA * NT == BM * KQ, "whole A quads per thread");
+    static_assert(BS != B_COLS || NB == 1 || NB == 2 || NB == 4, "columns per lane");
+    constexpr int RB = BS == B_PACKED ? O::BP : 2;  // 16-byte registers per block and chunk
+    __shared__ __attribute__((aligned(16))) char smem[D * STAGE];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WVN, wn = wave % WVN;
+    const int fr = lane & 15, fg = lane >> 4;
+
+    // tile coordinates: each XCD owns a contiguous run of tiles, walked along M
+    // first, so that the row tiles of one column strip share its B in that L2
+    const int64_t tiles_m = (p.M + BM - 1) / BM;
+    const int64_t tiles_n = (p.N + BN - 1) / BN;
+    int64_t bid = blockIdx.x;
+    {
+        const int64_t nb = gridDim.x, x = bid & 7, i = bid >> 3, q = nb >> 3, r = nb & 7;
+        bid = x * q + (x < r ? x : r) + i;
+    }
+    constexpr int GM = HEAL_GROUP_M;
+    const int64_t group = bid / (GM * tiles_n);
+    const int64_t first_m = group * GM;
+    const int64_t gm = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
+    const int64_t in_group = bid - group * GM * tiles_n;
+    const int64_t m0 = (first_m + in_group % gm) * BM;
+    const int64_t n0 = (in_group / gm) * BN;
+
+    const int64_t M = p.M, N = p.N;
+    const int K = (int)p.K;
+    const int ns = (K + BK - 1) / BK;
+    const int KC = (K + 31) / 32;
+    const int rows = (int)((M - m0) < BM ? (M - m0) : BM);
+    const int cols = (int)((N - n0) < BN ? (N - n0) : BN);
+    const int back_k = K < 4 ? 0 : (4 - (K & 3)) & 3;   // a quad across the end of K starts this much early
+
+    int a_kq[NA], a_row[NA], st_a[NA];
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+        const int q = tid - 64 * CW + NT * u;
+        a_row[u] = q / KQ;
+        a_kq[u] = q % KQ;
+        st_a[u] = L::quad_off(a_row[u], a_kq[u]);
+    }
+
+    for (int64_t b = blockIdx.y; b < p.batch; b += gridDim.y) {
+        const float *A = p.A + b * p.strideA + m0 * p.lda;
+        const int a_bytes = (int)(((int64_t)(rows - 1) * p.lda + K) * 4);
+        const char *B = reinterpret_cast<const char *>(p.B);
+        int b_bytes;
+        if constexpr (BS == B_PACKED) {
+            B += (n0 / 16) * KC * O::BP * 1024;
+            b_bytes = (cols + 15) / 16 * KC * O::BP * 1024;
+        } else if constexpr (BS == B_ROWS) {
+            B += (b * p.strideB + n0 * p.ldb) * 4;
+            b_bytes = (int)(((int64_t)(cols - 1) * p.ldb + K) * 4);
+        } else {
+            B += b * p.strideB * 4;              // from column 0: a lane may read back across n0
+            b_bytes = (int)(((int64_t)(K - 1) * p.ldb + N) * 4);
+        }
+
+        uint32_t va[NA];
+#pragma unroll
+        for (int u = 0; u < NA; ++u)
+            va[u] = a_row[u] < rows ? (uint32_t)((a_row[u] * p.lda + 4 * a_kq[u]) * 4) : kOOB;
+        uint32_t vb[NB];
+        // B_COLS: a lane's NB columns are NB*fr .. +NB-1 of the wave's; the lane
+        // whose columns cross the edge of B reads them back_n early
+        int back_n = 0;
+        const bool edge_n = BS == B_COLS && (wn + 1) * 16 * NB > cols;
+        if constexpr (BS == B_COLS) {
+            const int c = (wn * 16 + fr) * NB;
+            back_n = c < cols && c + NB > cols ? c + NB - cols : 0;
+            vb[0] = c < cols ? (uint32_t)((8 * fg * p.ldb + n0 + c - back_n) * 4) : kOOB;
+        } else {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int jb = wn * NB + j;
+                if constexpr (BS == B_PACKED)
+                    vb[j] = 16 * jb < cols ? (uint32_t)(jb * KC * O::BP * 1024 + lane * 16) : kOOB;
+                else
+                    vb[j] = 16 * jb + fr < cols
+                                ? (uint32_t)(((16 * jb + fr) * p.ldb + 8 * fg) * 4) : kOOB;
+            }
+        }
+
+        // Stage s of A, or chunk kc of B, into a register set.  Those
+        // past the last read nothing: every lane's offset lies beyond the buffer.
+        // The scalar offset stays inside the buffer (the last stage stands in
+        // for one past it); with a K tail the whole offset is the lane's own.
+        auto load_a = [&](u32x4 *ra, int s) {
+            const __amdgpu_buffer_rsrc_t r = make_rsrc(A, a_bytes);
+            const uint32_t past = past_end(s, ns);
+            const int so = (s < ns ? s : ns - 1) * BK * 4;
+#pragma unroll
+            for (int u = 0; u < NA; ++u) {
+                uint32_t v = va[u] | past;
+                if (TAIL) {
+                    const int k = s * BK + 4 * a_kq[u];
+                    v = k >= K || (v & kOOB) ? kOOB : v + so - (k + 4 > K ? 4u * back_k : 0u);
+                }
+                ra[u] = bload4(r, v, TAIL ? 0 : so);
+            }
+        };
+        auto load_b = [&](u32x4 (*rb)[RB], int c) {
+            const __amdgpu_buffer_rsrc_t r = make_rsrc(B, b_bytes);
+            const uint32_t past = past_end(c, ns * KS);
+            const int kc = c < ns * KS ? c : ns * KS - 1;
+            if constexpr (BS == B_COLS) {
+                float *v = reinterpret_cast<float *>(rb);
+                const uint32_t o = vb[0] | past;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int so = (kc * 32 + t) * (int)p.ldb * 4;
+                    uint32_t w = o;
+                    if (TAIL) w = kc * 32 + 8 * fg + t >= K || (o & kOOB) ? kOOB : o + so;
+                    bload_v<NB>(r, w, TAIL ? 0 : so, v + t * NB);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const uint32_t o = vb[j] | past;
+#pragma unroll
+                    for (int q = 0; q < RB; ++q) {
+                        const int so = kc * (BS == B_PACKED ? O::BP * 1024 : 128);
+                        uint32_t w = o + (BS == B_PACKED ? 1024u : 16u) * q;
+                        if (TAIL) {
+                            const int k = kc * 32 + (BS == B_PACKED ? 0 : 8 * fg + 4 * q);
+                            w = k >= K || (o & kOOB) ? kOOB : w + so;
+                            if (BS == B_ROWS && k < K && k + 4 > K && !(o & kOOB)) w -= 4u * back_k;
+                        }
+                        rb[j][q] = bload4(r, w, TAIL ? 0 : so);
+                    }
+                }
+            }
+        };
+        auto store_a = [&](char *st, const u32x4 *ra, int s) {
+#pragma unroll
+            for (int u = 0; u < NA; ++u) {
+                u32x4 q = ra[u];
+                if (TAIL && s == ns - 1 && s * BK + 4 * a_kq[u] + 4 > K) q = shift_quad(q, back_k);
+                const f32x4 x = __builtin_bit_cast(f32x4, q);
+                const float x0 = x.x, x1 = x.y, x2 = x.z, x3 = x.w;
+                const int off = st_a[u];
+                if constexpr (OP == OP_BASE) {
+                    *reinterpret_cast<u32x2 *>(st + off) = u32x2{cvt2_f16(x0, x1), cvt2_f16(x2, x3)};
+                } else {
+                    uint32_t h0, l0, h1, l1;
+                    if constexpr (OP == OP_FULL) {
+                        split2_f16(x0, x1, h0, l0);
+                        split2_f16(x2, x3, h1, l1);
+                    } else {
+                        split2(x0, x1, h0, l0);
+                        split2(x2, x3, h1, l1);
+                    }
+                    *reinterpret_cast<u32x2 *>(st + off) = u32x2{h0, h1};
+                    *reinterpret_cast<u32x2 *>(st + A_PLANE + off) = u32x2{l0, l1};
+                }
+            }
+        };
+
+        f32x4 acc[NB][MB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int i = 0; i < MB; ++i) acc[j][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+        // the two parts of B of chunk kc
+        auto frag_b = [&](const u32x4 (*rb)[RB], int kc, u32x4 *bh, u32x4 *bl) {
+            if constexpr (BS == B_PACKED) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    bh[j] = rb[j][0];
+                    if constexpr (OP == OP_FULL)   // the weight times 2^-10, for the residual product
+                        bl[j] = __builtin_bit_cast(
+                            u32x4, __builtin_bit_cast(f16x8, bh[j]) * (_Float16)0x1p-10f);
+                    else if constexpr (OP == OP_PRESPLIT)
+                        bl[j] = rb[j][RB - 1];
+                }
+            } else if constexpr (BS == B_ROWS) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        u32x4 r = rb[j][q];
+                        if (TAIL && kc == KC - 1 && kc * 32 + 8 * fg + 4 * q + 4 > K)
+                            r = shift_quad(r, back_k);
+                        const f32x4 x = __builtin_bit_cast(f32x4, r);
+                        uint32_t h0, l0, h1, l1;
+                        split2(x.x, x.y, h0, l0);
+                        split2(x.z, x.w, h1, l1);
+                        bh[j][2 * q] = h0;
+                        bh[j][2 * q + 1] = h1;
+                        bl[j][2 * q] = l0;
+                        bl[j][2 * q + 1] = l1;
+                    }
+                }
+            } else {
+                const float *v = reinterpret_cast<const float *>(rb);
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        float x0 = v[2 * t * NB + j], x1 = v[(2 * t + 1) * NB + j];
+                        if (NB > 1 && edge_n) {
+                            // column j of a lane that read back_n columns early
+#pragma unroll
+                            for (int c = j + 1; c < NB; ++c) {
+                                x0 = back_n == c - j ? v[2 * t * NB + c] : x0;
+                                x1 = back_n == c - j ? v[(2 * t + 1) * NB + c] : x1;
+                            }
+                        }
+                        uint32_t h, l;
+                        split2(x0, x1, h, l);
+                        bh[j][t] = h;
+                        bl[j][t] = l;
+                    }
+            }
+        };
+        auto frag_a = [&](const char *st, int ks, u32x4 *ah, u32x4 *al) {
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                const int off = L::chunk_off((wm * MB + i) * 16 + fr, 4 * ks + fg);
+                ah[i] = *reinterpret_cast<const u32x4 *>(st + off);
+                if (O::AP == 2) al[i] = *reinterpret_cast<const u32x4 *>(st + A_PLANE + off);
+            }
+        };
+        auto multiply = [&](const u32x4 *bh, const u32x4 *bl, const u32x4 *ah, const u32x4 *al) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int i = 0; i < MB; ++i) acc[j][i] = mma<O::BF16>(bh[j], ah[i], acc[j][i]);
+            if constexpr (OP == OP_FULL) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int i = 0; i < MB; ++i) acc[j][i] = mma<false>(bl[j], al[i], acc[j][i]);
+            } else if constexpr (O::BF16) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int i = 0; i < MB; ++i) acc[j][i] = mma<true>(bl[j], ah[i], acc[j][i]);
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int i = 0; i < MB; ++i) acc[j][i] = mma<true>(bh[j], al[i], acc[j][i]);
+            }
+        };
+
+        if (ns > 0 && wave < CW) {
+            u32x4 rb[RC][NB][RB];
+            constexpr int FP = PIPE ? 2 : 1;         // sets of A fragments
+            u32x4 ah[FP][MB], al[FP][MB], bh[2][NB], bl[2][NB];
+            // chunk c's packed B is multiplied out of its ring registers
+            auto mul = [&](int f, int n) {
+                if constexpr (BS == B_PACKED) {
+                    u32x4 wh[NB], wl[NB];
+                    frag_b(rb[n], 0, wh, wl);
+                    multiply(wh, wl, ah[f % FP], al[f % FP]);
+                } else {
+                    multiply(bh[f], bl[f], ah[f % FP], al[f % FP]);
+                }
+            };
+#pragma unroll
+            for (int c = 0; c < RC; ++c) {
+                load_b(rb[c], c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __syncthreads();
+            if (PIPE) frag_a(smem, 0, ah[0], al[0]);
+            if constexpr (BS != B_PACKED) {
+                frag_b(rb[0], 0, bh[0], bl[0]);
+                __builtin_amdgcn_sched_barrier(0);
+                load_b(rb[0], RC);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // While a chunk is multiplied, the next one's fragments of A are
+            // read from LDS (its stage is complete: the loaders are a stage
+            // ahead) and its B is split; then the registers of B that were read
+            // are reloaded RC chunks ahead.
+            int buf = 0;
+            auto stage = [&](int t, int s, bool reload) {
+                const char *cur = smem + buf;
+                buf = buf == 2 * STAGE ? 0 : buf + STAGE;
+                const char *nxt = smem + buf;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const int c = t * KS + ks;                 // chunk of the trip
+                    constexpr int TC = T * KS;
+                    const int f = c & 1, g = f ^ 1, m = c % RC, n = (c + 1) % TC % RC;
+                    if constexpr (PIPE)
+                        frag_a(ks + 1 < KS ? cur : nxt, (ks + 1) % KS, ah[g % FP], al[g % FP]);
+                    else
+                        frag_a(cur, ks, ah[0], al[0]);
+                    if constexpr (BS != B_PACKED) frag_b(rb[n], s * KS + ks + 1, bh[g], bl[g]);
+                    mul(f, m);
+                    constexpr int NM = MB * NB * (OP == OP_BASE ? 1 : OP == OP_FULL ? 2 : 3);
+                    constexpr int ND = MB * O::AP;
+                    constexpr int NV = BS == B_PACKED ? (OP == OP_FULL ? 4 * NB : 0) : 26 * NB;
+                    constexpr int PV = (NV + NM - 1) / NM;
+                    constexpr int PD = (ND + NM - 1) / NM;
+                    // LDS reads and the split's VALU work between the MFMAs
+#pragma unroll
+                    for (int x = 0; PIPE && x < NM; ++x) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        if (x * PD < ND) __builtin_amdgcn_sched_group_barrier(0x100, PD, 0);
+                        if (PV) __builtin_amdgcn_sched_group_barrier(0x002, PV, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (reload) {
+                        if constexpr (BS == B_PACKED) load_b(rb[m], s * KS + ks + RC);
+                        else load_b(rb[n], s * KS + ks + 1 + RC);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __syncthreads();
+            };
+            int s0 = 0;
+            for (; s0 + T <= ns; s0 += T) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) stage(t, s0 + t, true);
+            }
+#pragma unroll
+            for (int t = 0; t + 1 < T; ++t)
+                if (s0 + t < ns) stage(t, s0 + t, false);
+            const int whole = (ns + RA - 1) / RA * RA;       // the loaders' whole groups
+            for (int s = ns; s < whole; ++s) __syncthreads();
+        } else if (ns > 0) {
+            u32x4 ra[RA][NA];
+#pragma unroll
+            for (int t = 0; t < RA; ++t) {
+                load_a(ra[t], t);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                store_a(smem + t * STAGE, ra[t], t);
+                load_a(ra[t], RA + t);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __syncthreads();
+            int buf = 2 * STAGE;
+            for (int s0 = 0; s0 < ns; s0 += RA) {
+#pragma unroll
+                for (int t = 0; t < RA; ++t) {
+                    const int s = s0 + t;
+                    store_a(smem + buf, ra[(t + 2) % RA], s + 2);
+                    buf = buf == 2 * STAGE ? 0 : buf + STAGE;
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_a(ra[(t + 2) % RA], s + 2 + RA);
+                    __syncthreads();
+                }
+            }
+        }
+        if (wave >= CW) {
+            if (b + gridDim.y < p.batch) __syncthreads();
+            continue;
+        }
+
+        float *__restrict__ C = p.C + b * p.strideC;
+        auto scaled = [&](float x) {
+            if constexpr (OP == OP_BASE || OP == OP_FULL) return ldexpf(x, -p.e);
+            if constexpr (OP == OP_BF16X3) return p.alpha == 1.0f ? x : x * p.alpha;
+            return x;
+        };
+        auto store_c = [&](int64_t m, int64_t n, f32x4 v) {
+            if (m < M && n < N) {
+                float *cp = C + m * p.ldc + n;
+                if (n + 4 <= N) {
+                    *reinterpret_cast<f32x4_u *>(cp) = v;
+                } else {
+                    cp[0] = v.x;
+                    if (n + 1 < N) cp[1] = v.y;
+                    if (n + 2 < N) cp[2] = v.z;
+                }
+            }
+        };
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+            const int64_t m = m0 + (wm * MB + i) * 16 + fr;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                f32x4 v;
+                int64_t n = n0 + wn * 16 * NB;
+                if constexpr (BS == B_COLS) {
+                    // the lane's 4 NB results are columns 4 NB fg .. of the wave's,
+                    // result e of block c at NB e + c
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        v[t] = scaled(acc[(4 * j + t) % NB][i][(4 * j + t) / NB]);
+                    n += 4 * NB * fg + 4 * j;
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) v[t] = scaled(acc[j][i][t]);
+                    n += 16 * j + 4 * fg;
+                }
+                store_c(m, n, v);
+            }
+        }
+        if (b + gridDim.y < p.batch) __syncthreads();  // LDS reuse by the next batch entry
+    }
+}
+
+template <int OP, int BS, int MB, int WVM, int NB, int WVN, int KS, int RC, int LW, int RA, bool PIPE>
+hipError_t launch_cfg(const DirectArgs &a, hipStream_t stream)
+{
+    constexpr int BM = 16 * MB * WVM, BN = 16 * NB * WVN;
+    const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+    const dim3 grid((unsigned)tiles, (unsigned)(a.batch < 65535 ? a.batch : 65535));
+    const dim3 block(64 * (WVM * WVN + LW));
+    if (a.K % (32 * KS))
+        hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, true>),
+                           grid, block, 0, stream, a);
+    else
+        hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, false>),
+                           grid, block, 0, stream, a);
+    return hipGetLastError();
+}
+
+// Tile configurations (rows x columns of the tile).
+enum Cfg : int { T32x32, T32x64, T32x128, T64x64, T64x128, T96x128, T128x128, T128x256, T_COUNT };
+constexpr int kTileM[T_COUNT] = {32, 32, 32, 64, 64, 96, 128, 128};
+constexpr int kTileN[T_COUNT] = {32, 64, 128, 64, 128, 128, 128, 256};
+
+template <int OP, int BS>
+hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
+{
+    constexpr bool PACKED = BS == B_PACKED;
+    switch (cfg) {
+    //                                      MB WVM NB WVN KS RC LW RA PIPE
+    case T32x32: return launch_cfg<OP, BS, 2, 1, 1, 2, 2, 4, 2, 2, true>(a, stream);
+    case T32x64: return launch_cfg<OP, BS, 2, 1, 1, 4, 2, 4, 4, 2, true>(a, stream);
+    case T64x128: return launch_cfg<OP, BS, 4, 1, 2, 4, 2, 4, 4, 4, true>(a, stream);
+    case T128x128: return launch_cfg<OP, BS, 8, 1, 2, 4, 2, 2, 4, 2, false>(a, stream);
+    case T96x128:
+        if constexpr (PACKED) return launch_cfg<OP, BS, 6, 1, 2, 4, 2, 4, 4, 4, false>(a, stream);
+        else return launch_cfg<OP, BS, 6, 1, 2, 4, 2, 2, 4, 2, false>(a, stream);
+    case T32x128:
+        if constexpr (PACKED) return launch_cfg<OP, BS, 2, 1, 2, 4, 2, 4, 4, 4, true>(a, stream);
+        break;
+    case T64x64:
+        if constexpr (!PACKED) return launch_cfg<OP, BS, 4, 1, 1, 4, 4, 4, 4, 2, true>(a, stream);
+        break;
+    case T128x256:
+        if constexpr (OP == OP_FULL) return launch_cfg<OP, BS, 4, 2, 4, 4, 2, 2, 4, 2, false>(a, stream);
+        break;
+    }
+    return hipErrorInvalidValue;
+}
+
+// Time of one launch by configuration: us at 4096 deep with 64 tiles, with 256
+// (one per CU), and per further 256 tiles (0: one tile per CU at a time, so
+// whole rounds).  Measured on 128 to 3072 x 4096 x 4096 products; the last row
+// is the 256 x 256 tiles of the large kernels.  Other depths scale all alike.
+// The smallest of these estimates picks the tile; 0 in the middle: not built.
+struct Cost { float few, full, more; };
+constexpr Cost kCost[5][T_COUNT + 1] = {
+    // 32x32            32x64               32x128              64x64            64x128
+    // 96x128           128x128             128x256             large
+    /* HEAL-Base */
+    {{13, 15, 7.5f}, {14, 17.6f, 11}, {17.5f, 19.4f, 16}, {0, 0, 0}, {23.1f, 28, 0},
+     {29, 38.4f, 0}, {39.5f, 50.6f, 0}, {0, 0, 0}, {82, 122, 0}},
+    /* HEAL-Full */
+    {{15, 18.5f, 8.8f}, {16, 21, 13.3f}, {19.8f, 25.6f, 21}, {0, 0, 0}, {29.9f, 40.4f, 0},
+     {43.3f, 57.5f, 0}, {57, 74.5f, 0}, {93, 134, 0}, {150, 216, 0}},
+    /* (INT16 scores: not here) */
+    {},
+    /* pre-split */
+    {{17, 20, 11.5f}, {18, 22.2f, 17.5f}, {27.3f, 31.8f, 30}, {0, 0, 0}, {37.6f, 49.5f, 0},
+     {53.2f, 74, 0}, {64.7f, 92.7f, 0}, {0, 0, 0}, {185, 273, 0}},
+    /* bf16x3, B stored K x N (N x K below) */
+    {{24, 28, 14}, {27, 31.7f, 23}, {0, 0, 0}, {36, 40.6f, 40}, {61.3f, 66.3f, 0},
+     {66, 83.7f, 0}, {76.9f, 107.3f, 0}, {0, 0, 0}, {200, 283, 0}},
+};
+constexpr Cost kCostRows[T_COUNT + 1] = {
+    {28, 32, 18}, {30, 35, 32}, {0, 0, 0}, {39, 41.9f, 41}, {68, 70.5f, 0},
+    {72, 87.8f, 0}, {81, 111, 0}, {0, 0, 0}, {200, 283, 0}};
+
+float estimate(const Cost &c, int64_t tiles, int cus)
+{
+    const float r = (float)tiles / (float)cus;
+    if (r <= 1.0f) return c.few + (c.full - c.few) * (r < 0.25f ? 0.0f : (r - 0.25f) / 0.75f);
+    if (c.more > 0.0f) return c.full + (r - 1.0f) * c.more;
+    return c.full * (float)((tiles + cus - 1) / cus);
+}
+
+}  // namespace
+
+int direct_plan(int op, bool trans_b, const DirectArgs &a)
+{
+    // whole quads or columns to shift within a row; 32-bit byte offsets within
+    // a tile's rows of A, a tile of B, or all of B stored K x N (one stage
+    // past its end for the clamped index)
+    const int64_t lim = 0x7fffffffLL;
+    const bool rows = op == OP_BF16X3 && trans_b, cols = op == OP_BF16X3 && !trans_b;
+    if (a.K < 4 || a.K > (1 << 28) || ((int64_t)127 * a.lda + a.K + 128) * 4 >= lim) return -1;
+    if (rows && ((int64_t)255 * a.ldb + a.K + 128) * 4 >= lim) return -1;
+    if (cols && (a.N < 4 || (a.K + 128) * a.ldb * 4 >= lim)) return -1;
+    const int cus = device_cus();
+    const Cost *cost = rows ? kCostRows : kCost[op];
+    auto tiles = [&](int64_t bm, int64_t bn) {
+        return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.batch;
+    };
+    // the large kernels' tiles: a part-empty round costs less than a whole
+    // one (a power-limited chip runs fewer tiles faster)
+    const int64_t nl = tiles(256, 256);
+    float best = estimate(cost[T_COUNT], nl, cus);
+    if (nl > cus) best = 0.5f * (best + cost[T_COUNT].full * (float)nl / (float)cus);
+    int cfg = -1;
+    for (int c = 0; c < T_COUNT; ++c) {
+        const int64_t n = tiles(kTileM[c], kTileN[c]);
+        if (cost[c].full <= 0.0f || n > (1 << 20)) continue;
+        const float t = estimate(cost[c], n, cus);
+        if (t < best) {
+            best = t;
+            cfg = c;
+        }
+    }
+    return cfg;
+}
+
+hipError_t launch_direct(int op, bool trans_b, int cfg, const DirectArgs &a, hipStream_t stream)
+{
+    switch (op) {
+    case OP_BASE: return launch_tile<OP_BASE, B_PACKED>(cfg, a, stream);
+    case OP_FULL: return launch_tile<OP_FULL, B_PACKED>(cfg, a, stream);
+    case OP_PRESPLIT: return launch_tile<OP_PRESPLIT, B_PACKED>(cfg, a, stream);
+    case OP_BF16X3:
+        return trans_b ? launch_tile<OP_BF16X3, B_ROWS>(cfg, a, stream)
+                       : launch_tile<OP_BF16X3, B_COLS>(cfg, a, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace heal

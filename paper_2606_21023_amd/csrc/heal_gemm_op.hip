@@ -1374,22 +1374,6 @@ hipError_t launch_cfg(const OpArgs &a, hipStream_t stream)
 #define HEAL_OP_LARGE_PRESPLIT_N224_CFG 256, 224, 64, 112, 512, 32
 #endif
 
-// Compute units of the current device, queried once per device.
-int device_cus()
-{
-    constexpr int kMaxDev = 64;
-    static std::atomic<int> cache[kMaxDev];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) return 256;
-    int n = cache[dev].load(std::memory_order_relaxed);
-    if (n > 0) return n;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        n <= 0)
-        n = 256;
-    cache[dev].store(n, std::memory_order_relaxed);
-    return n;
-}
-
 // Relative time of a grid of 256 x bn tiles: the 256 x 256 instances hold
 // one workgroup per CU (LDS), so the grid runs in ceil(workgroups / CUs)
 // rounds, each as long as one tile, which grows with bn at fixed K.
@@ -1487,12 +1471,42 @@ hipError_t launch_op(int instance, const OpArgs &a, hipStream_t stream)
 
 }  // namespace
 
+// Compute units of the current device, queried once per device.
+int device_cus()
+{
+    constexpr int kMaxDev = 64;
+    static std::atomic<int> cache[kMaxDev];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) return 256;
+    int n = cache[dev].load(std::memory_order_relaxed);
+    if (n > 0) return n;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        n <= 0)
+        n = 256;
+    cache[dev].store(n, std::memory_order_relaxed);
+    return n;
+}
+
 hipError_t launch_gemm_op(int op, int instance, const OpArgs &a, hipStream_t stream)
 {
-    if (instance == HEAL_INSTANCE_AUTO)
-        instance = a.M <= 64 ? HEAL_INSTANCE_SKINNY
-                   : a.M * a.N <= (int64_t)2048 * 2048 ? HEAL_INSTANCE_MEDIUM
-                                                       : HEAL_INSTANCE_LARGE;
+    if (instance == HEAL_INSTANCE_AUTO) {
+        instance = select_instance(a.M, a.N);
+        if (op != OP_SCORES && instance != HEAL_INSTANCE_SKINNY) {
+            DirectArgs d = {};
+            d.M = a.M;
+            d.N = a.N;
+            d.K = a.K;
+            d.A = static_cast<const float *>(a.A);
+            d.lda = a.lda;
+            d.B = a.B;
+            d.C = a.C;
+            d.ldc = a.ldc;
+            d.batch = a.batch;
+            d.e = a.e;
+            const int cfg = direct_plan(op, false, d);
+            if (cfg >= 0) return launch_direct(op, false, cfg, d, stream);
+        }
+    }
     switch (op) {
     case OP_BASE: return launch_op<OP_BASE>(instance, a, stream);
     case OP_FULL: return launch_op<OP_FULL>(instance, a, stream);

@@ -23,7 +23,10 @@ struct GemmArgs {
     int vecC;  // C rows can be written with 16-byte stores
 };
 
-// Instance ids follow heal_instance_t in heal.h.
+// The instance of an M x N output by size (heal_instance_t in heal.h).
+int select_instance(int64_t M, int64_t N);
+
+// instance: HEAL_INSTANCE_*; AUTO chooses, the direct-B kernel included.
 hipError_t launch_gemm(int instance, const GemmArgs &args, bool trans_b, bool use_alpha,
                        hipStream_t stream);
 
@@ -62,6 +65,7 @@ enum OpKind : int {
     OP_FULL = 1,      // HEAL-Full: (A_hi * W16) + 2^-10 (A_lo * W16)
     OP_SCORES = 2,    // HEAL+ scores: dual-FP16 of INT16 Q and K, four products
     OP_PRESPLIT = 3,  // bf16x3 with B pre-split and packed
+    OP_BF16X3 = 4,    // bf16x3 with B split on the way in (heal_gemm_direct.hip only)
 };
 
 // One strided-batched product of heal_gemm_op.hip; sizes in elements.
@@ -83,6 +87,28 @@ struct OpArgs {
 // The INT16 scores on the short-K panel kernel (heal_gemm_panel.hip).
 bool scores_panel_applies(const OpArgs &args);
 hipError_t launch_scores_panel(const OpArgs &args, hipStream_t stream);
+
+// One product of heal_gemm_direct.hip; sizes and strides in elements.
+struct DirectArgs {
+    int64_t M, N, K;
+    const float *A;
+    int64_t lda, strideA;
+    const void *B;              // packed uint16, or FP32 (N x K or K x N)
+    int64_t ldb, strideB;
+    float *C;
+    int64_t ldc, strideC;
+    int64_t batch;
+    int e;                      // BASE, FULL: C is scaled by 2^-e
+    float alpha;                // BF16X3
+};
+
+// The tile configuration of the direct-B kernel that a product should take, or
+// -1 where it cannot run the call or the large kernels are faster (host only).
+int direct_plan(int op, bool trans_b, const DirectArgs &args);
+hipError_t launch_direct(int op, bool trans_b, int cfg, const DirectArgs &args, hipStream_t stream);
+
+// Compute units of the current device, queried once per device.
+int device_cus();
 
 // instance: HEAL_INSTANCE_* (AUTO chooses from M and N).
 hipError_t launch_gemm_op(int op, int instance, const OpArgs &args, hipStream_t stream);

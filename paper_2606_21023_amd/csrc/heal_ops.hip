@@ -16,14 +16,19 @@ constexpr int kThreads = 256;
 // Streaming kernels take one step per thread up to the grid limit (the loops
 // stride only past it): capping the grid at 4096 workgroups that stride over
 // the rest cost 10-15% of HBM bandwidth on the standalone splits.  The max|x|
-// reduction folds one atomic per workgroup into a single word, so it keeps a
-// small grid whose threads stride with four loads in flight (max|x| of 64M
-// elements: 512 workgroups 43 us, 1024 49 us, 2048 53 us, 4096 67 us, 8192
-// 106 us).
+// reduction folds one atomic per workgroup into a single word, some 10 ns each
+// one after another, so it keeps 256 workgroups of 512 threads that stride with
+// four loads in flight (max|x| of 2M / 6.3M / 33.5M elements: 6.9 / 9.5 / 23.3
+// us; 512 workgroups of 256 threads 9.7 / 12.1 / 25.9, 1024 of them 9.7 / 18.0 /
+// 31.9, 128 of 512 threads 5.8 / 9.2 / 30.2, 256 of 1024 5.9 / 9.5 / 23.9).
 constexpr int64_t kMaxBlocks = 0x40000000LL;
 #ifndef HEAL_REDUCE_BLOCKS
-#define HEAL_REDUCE_BLOCKS 512
+#define HEAL_REDUCE_BLOCKS 256
 #endif
+#ifndef HEAL_REDUCE_THREADS
+#define HEAL_REDUCE_THREADS 512
+#endif
+constexpr int kReduceThreads = HEAL_REDUCE_THREADS;
 
 int64_t blocks_for(int64_t work, int64_t per_block, int64_t cap = kMaxBlocks)
 {
@@ -124,18 +129,18 @@ __global__ void zero_word_kernel(uint32_t *w) { *w = 0u; }
 // its elements and folds the result into *out with one atomic maximum on the
 // bit pattern (for non-negative floats the unsigned order of the patterns is
 // the numeric order, and a maximum is independent of the order of the folds).
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kReduceThreads)
 maxabs_kernel(const float *__restrict__ x, int64_t rows, int64_t cols, int64_t ld,
               uint32_t *__restrict__ out)
 {
     const int64_t n = rows * cols;
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    const int64_t stride = (int64_t)gridDim.x * kReduceThreads;
     uint32_t m = 0u;
     if (ld == cols && (reinterpret_cast<uintptr_t>(x) & 15u) == 0) {
         const int64_t n4 = n / 4;
         const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
         // four 16-byte loads in flight per thread and trip
-        for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n4; i += 4 * stride) {
+        for (int64_t i = (int64_t)blockIdx.x * kReduceThreads + threadIdx.x; i < n4; i += 4 * stride) {
             u32x4 b[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
@@ -147,10 +152,10 @@ maxabs_kernel(const float *__restrict__ x, int64_t rows, int64_t cols, int64_t l
 #pragma unroll
                 for (int t = 0; t < 4; ++t) m = max(m, b[u][t] & 0x7fffffffu);
         }
-        for (int64_t i = 4 * n4 + (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride)
+        for (int64_t i = 4 * n4 + (int64_t)blockIdx.x * kReduceThreads + threadIdx.x; i < n; i += stride)
             m = max(m, __builtin_bit_cast(uint32_t, x[i]) & 0x7fffffffu);
     } else {
-        for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
+        for (int64_t i = (int64_t)blockIdx.x * kReduceThreads + threadIdx.x; i < n; i += stride) {
             const int64_t r = i / cols, c = i - r * cols;
             m = max(m, __builtin_bit_cast(uint32_t, x[r * ld + c]) & 0x7fffffffu);
         }
@@ -158,13 +163,13 @@ maxabs_kernel(const float *__restrict__ x, int64_t rows, int64_t cols, int64_t l
     // wave, then workgroup reduction
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
-    __shared__ uint32_t part[kThreads / 64];
+    __shared__ uint32_t part[kReduceThreads / 64];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t b = part[0];
 #pragma unroll
-        for (int w = 1; w < kThreads / 64; ++w) b = max(b, part[w]);
+        for (int w = 1; w < kReduceThreads / 64; ++w) b = max(b, part[w]);
         atomicMax(out, b);
     }
 }
@@ -178,21 +183,27 @@ maxabs_kernel(const float *__restrict__ x, int64_t rows, int64_t cols, int64_t l
 // that is a half-integer is representable and comes out exactly, so rint
 // takes the even side.  The quotient stays within 32767 in magnitude for any
 // m > 0, however small.
-__device__ __forceinline__ int code_i16(float x, double m)
+// An FP64 division is some thirty instructions, so the product with inv = 1/m
+// stands in for it: two roundings of a value below 2^15, off by less than
+// 2^-36, decide every quotient that is further than 2^-30 from a half-integer
+// alike; the others (two in 10^9) are divided.
+__device__ __forceinline__ int code_i16(float x, double m, double inv)
 {
-    return (int)__builtin_rint((32767.0 * (double)x) / m);
+    const double n = 32767.0 * (double)x, p = n * inv;
+    double r = __builtin_rint(p);
+    if (__builtin_expect(__builtin_fabs(p - r) > 0.5 - 0x1p-30, 0)) r = __builtin_rint(n / m);
+    return (int)r;
 }
 
 // INT16 codes q = Round(32767 x / m), m = max|X| read from *maxabs (m = 0
-// gives all-zero codes).  HBM-bound: the FP64 division per element hides
-// behind the 6 bytes each element moves.
+// gives all-zero codes).  HBM-bound.
 __global__ void __launch_bounds__(kThreads)
 quantize_kernel(const float *__restrict__ x, int64_t n, int16_t *__restrict__ q,
                 const float *__restrict__ maxabs)
 {
     const float mf = *maxabs;
     const bool zero = !(mf > 0.0f);
-    const double m = zero ? 1.0 : (double)mf;
+    const double m = zero ? 1.0 : (double)mf, inv = 1.0 / m;
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     int64_t done = 0;
@@ -207,8 +218,8 @@ quantize_kernel(const float *__restrict__ x, int64_t n, int16_t *__restrict__ q,
             u32x4 o;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const int c0 = zero ? 0 : code_i16(v[2 * t], m);
-                const int c1 = zero ? 0 : code_i16(v[2 * t + 1], m);
+                const int c0 = zero ? 0 : code_i16(v[2 * t], m, inv);
+                const int c1 = zero ? 0 : code_i16(v[2 * t + 1], m, inv);
                 o[t] = ((uint32_t)c0 & 0xffffu) | ((uint32_t)c1 << 16);
             }
             __builtin_nontemporal_store(o, q4 + i);
@@ -216,7 +227,66 @@ quantize_kernel(const float *__restrict__ x, int64_t n, int16_t *__restrict__ q,
         done = n8 * 8;
     }
     for (int64_t i = done + t0; i < n; i += stride)
-        q[i] = (int16_t)(zero ? 0 : code_i16(x[i], m));
+        q[i] = (int16_t)(zero ? 0 : code_i16(x[i], m, inv));
+}
+
+// The maximum and the codes of a small tensor in one workgroup and one launch:
+// every element is read once and kept in registers between the two.  A decode
+// step's queries (32 heads x 128: 4096 elements) take 2.8 us on the GPU, 5.4
+// with the three launches of larger tensors, and a third of the host's time;
+// 16384 elements 4.0 against 6.0, 32768 7.8 against 6.1, so the line lies
+// between.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallQuads = 4;                              // per thread
+constexpr int64_t kSmallQuantize = 4 * kSmallThreads * kSmallQuads;
+
+__global__ void __launch_bounds__(kSmallThreads)
+quantize_small_kernel(const float *__restrict__ x, int n, int16_t *__restrict__ q,
+                      float *__restrict__ maxabs)
+{
+    const int tid = threadIdx.x, n4 = n / 4;
+    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
+    f32x4 v[kSmallQuads];
+    uint32_t m = 0u;
+#pragma unroll
+    for (int u = 0; u < kSmallQuads; ++u) {
+        const int i = u * kSmallThreads + tid;
+        v[u] = i < n4 ? x4[i] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    const float tail = tid < n - 4 * n4 ? x[4 * n4 + tid] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < kSmallQuads; ++u) {
+        const u32x4 b = __builtin_bit_cast(u32x4, v[u]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) m = max(m, b[t] & 0x7fffffffu);
+    }
+    m = max(m, __builtin_bit_cast(uint32_t, tail) & 0x7fffffffu);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+    __shared__ uint32_t part[kSmallThreads / 64];
+    if ((tid & 63) == 0) part[tid >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSmallThreads / 64; ++w) m = max(m, part[w]);
+    const float mf = __builtin_bit_cast(float, m);
+    if (tid == 0) *maxabs = mf;
+    const bool zero = !(mf > 0.0f);
+    const double md = zero ? 1.0 : (double)mf, inv = 1.0 / md;
+    u32x2 *q4 = reinterpret_cast<u32x2 *>(q);
+#pragma unroll
+    for (int u = 0; u < kSmallQuads; ++u) {
+        const int i = u * kSmallThreads + tid;
+        if (i >= n4) break;
+        u32x2 o;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int c0 = zero ? 0 : code_i16(v[u][2 * t], md, inv);
+            const int c1 = zero ? 0 : code_i16(v[u][2 * t + 1], md, inv);
+            o[t] = ((uint32_t)c0 & 0xffffu) | ((uint32_t)c1 << 16);
+        }
+        q4[i] = o;
+    }
+    if (tid < n - 4 * n4) q[4 * n4 + tid] = (int16_t)(zero ? 0 : code_i16(tail, md, inv));
 }
 
 }  // namespace
@@ -270,14 +340,21 @@ hipError_t launch_maxabs(const float *x, int64_t rows, int64_t cols, int64_t ld,
     const int64_t n = rows * cols;
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(maxabs_kernel,
-                       dim3((unsigned)blocks_for(n, (int64_t)kThreads * 16, HEAL_REDUCE_BLOCKS)),
-                       dim3(kThreads), 0, stream, x, rows, cols, ld, w);
+                       dim3((unsigned)blocks_for(n, (int64_t)kReduceThreads * 16, HEAL_REDUCE_BLOCKS)),
+                       dim3(kReduceThreads), 0, stream, x, rows, cols, ld, w);
     return hipGetLastError();
 }
 
 hipError_t launch_quantize(const float *x, int64_t n, int16_t *q, float *maxabs,
                            hipStream_t stream)
 {
+    // one workgroup up to 16384 elements (16-byte aligned x, 8-byte aligned q)
+    if (n > 0 && n <= kSmallQuantize && (reinterpret_cast<uintptr_t>(x) & 15u) == 0 &&
+        (reinterpret_cast<uintptr_t>(q) & 7u) == 0) {
+        hipLaunchKernelGGL(quantize_small_kernel, dim3(1), dim3(kSmallThreads), 0, stream, x, (int)n,
+                           q, maxabs);
+        return hipGetLastError();
+    }
     hipError_t err = launch_maxabs(x, 1, n, n, maxabs, stream);
     if (err != hipSuccess || n == 0) return err;
     hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)blocks_for(n, (int64_t)kThreads * 8)),

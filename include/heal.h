@@ -129,10 +129,16 @@ heal_status_t heal_gemm_f32_strided_batched(int64_t M, int64_t N, int64_t K, flo
                                             int64_t batch, hipStream_t stream);
 
 /*
- * Kernel instances.  The instance is normally chosen from (M, N) alone.
- * heal_gemm_f32_instance forces one, for tests of cross-instance bitwise
- * equality and for tuning; every instance computes the same bits.
- *   instance : one of heal_instance_t; HEAL_INSTANCE_AUTO chooses as usual.
+ * Kernel instances.  heal_gemm_f32_instance forces one, for tests of
+ * cross-instance bitwise equality and for tuning; every instance computes the
+ * same bits.
+ *   instance : one of heal_instance_t; HEAL_INSTANCE_AUTO chooses as usual, by
+ *   sizes, layout and alignment, between these and two more kernels: the panel
+ *   kernel for B stored N x K with K <= 128 (attention scores: bf16x3 with
+ *   trans_b = 1, which the large and medium instances take too from 256 rows,
+ *   and the INT16 scores), where a panel of A stays in LDS while the workgroup
+ *   walks the columns of C; and the direct-B kernel, whose smaller tiles fill
+ *   the chip where the output has too few large ones.
  * Other arguments as heal_gemm_f32_strided_batched.
  */
 typedef enum heal_instance_t {
@@ -141,14 +147,7 @@ typedef enum heal_instance_t {
                                   products take 256 x 224 where that needs fewer
                                   rounds of workgroups; INT16 scores 128 x 256),
                                   compute-bound shapes */
-    HEAL_INSTANCE_MEDIUM = 2,  /* 128 x 128 output tiles.  On this and the large
-                                  instance, products with B stored N x K and
-                                  K <= 128 (attention scores: bf16x3 with
-                                  trans_b = 1, and the INT16 scores) whose rows
-                                  are 16-byte aligned run a panel kernel instead:
-                                  a 256-row (bf16x3) or 128-row (INT16) panel of
-                                  A stays in LDS while the workgroup walks the
-                                  columns of C (at least one panel of rows) */
+    HEAL_INSTANCE_MEDIUM = 2,  /* 128 x 128 output tiles */
     HEAL_INSTANCE_SKINNY = 3,  /* M <= 64: decode and lm_head shapes, B streamed */
     HEAL_INSTANCE_COUNT = 4
 } heal_instance_t;
@@ -160,7 +159,8 @@ heal_status_t heal_gemm_f32_instance(int instance, int64_t M, int64_t N, int64_t
                                      float *C, int64_t ldc, int64_t strideC,
                                      int64_t batch, hipStream_t stream);
 
-/* The instance heal_gemm_f32 would choose for an M x N output (no HIP call). */
+/* The instance heal_gemm_f32 would choose for an M x N output by its size, where
+ * neither the panel nor the direct-B kernel takes the product (no HIP call). */
 int heal_gemm_select_instance(int64_t M, int64_t N);
 
 /* ==========================================================================

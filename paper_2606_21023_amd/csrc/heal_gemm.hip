@@ -614,9 +614,9 @@ hipError_t launch_gemm(int instance, const GemmArgs &a, bool trans_b, bool use_a
                        hipStream_t stream)
 {
     if (instance == HEAL_INSTANCE_AUTO) {
+        if (HEAL_PANEL && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
         instance = select_instance(a.M, a.N);
-        if (instance != HEAL_INSTANCE_SKINNY &&
-            !(HEAL_PANEL && panel_kernel_applies(a, trans_b))) {
+        if (instance != HEAL_INSTANCE_SKINNY) {
             DirectArgs d = {};
             d.M = a.M;
             d.N = a.N;
@@ -638,11 +638,11 @@ hipError_t launch_gemm(int instance, const GemmArgs &a, bool trans_b, bool use_a
     }
     switch (instance) {
     case HEAL_INSTANCE_LARGE:
-        if (HEAL_PANEL && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
+        if (HEAL_PANEL && a.M >= 256 && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
         if (large_kernel_applies(a, trans_b)) return launch_gemm_large(a, trans_b, use_alpha, stream);
         return launch_tile<HEAL_LARGE_CFG>(a, trans_b, use_alpha, stream);
     case HEAL_INSTANCE_MEDIUM:
-        if (HEAL_PANEL && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
+        if (HEAL_PANEL && a.M >= 256 && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
         return launch_tile<HEAL_MEDIUM_CFG>(a, trans_b, use_alpha, stream);
     case HEAL_INSTANCE_SKINNY:
         if (skinny_kernel_applies(a, trans_b)) return launch_gemm_skinny(a, trans_b, use_alpha, stream);

@@ -1419,10 +1419,6 @@ hipError_t launch_large(const OpArgs &a, hipStream_t stream)
 template <int OP>
 hipError_t launch_op(int instance, const OpArgs &a, hipStream_t stream)
 {
-    if constexpr (OP == OP_SCORES) {
-        if (HEAL_PANEL && instance != HEAL_INSTANCE_SKINNY && scores_panel_applies(a))
-            return launch_scores_panel(a, stream);
-    }
     switch (instance) {
     case HEAL_INSTANCE_LARGE: return launch_large<OP>(a, stream);
     case HEAL_INSTANCE_MEDIUM: return launch_cfg<OP, HEAL_OP_MEDIUM_CFG>(a, stream);
@@ -1490,6 +1486,7 @@ int device_cus()
 hipError_t launch_gemm_op(int op, int instance, const OpArgs &a, hipStream_t stream)
 {
     if (instance == HEAL_INSTANCE_AUTO) {
+        if (HEAL_PANEL && op == OP_SCORES && scores_panel_applies(a)) return launch_scores_panel(a, stream);
         instance = select_instance(a.M, a.N);
         if (op != OP_SCORES && instance != HEAL_INSTANCE_SKINNY) {
             DirectArgs d = {};

@@ -8,7 +8,16 @@
 //    into two exact FP16 parts (hi, q - hi), four products, the sum scaled
 //    by alpha (maxQ/32767)(maxK/32767).
 //
-// Such products are bound by writing C: every output element costs 4 bytes
+// Rows of C of any length and alignment are taken (RAG): half lines at the ends
+// of the pieces a store writes have to meet in L2, so these are plain stores
+// (32 heads of 1531 x 1531 x 128: bf16x3 276.8 us and INT16 172.7 on tiles,
+// 130.5 and 114.7 here, 245.7 and 225.8 with non-temporal stores), and the last
+// one to three columns of a row are stored by element.  Panels of 16, 32 and
+// 64 rows take the few-query products, bound by reading B (TURN below: 32
+// heads of 1 x 3001 x 128 INT16 44.6 -> 8.6 us, 17.3 with B read in fragment
+// order).
+//
+// The others are bound by writing C: every output element costs 4 bytes
 // of HBM writes against 2K or 4K multiply-adds, so the kernel is built to
 // keep the write stream busy.  A workgroup owns a panel of 128 or 256 rows
 // of A (one batch entry), splits it once into LDS, and then walks its share
@@ -32,6 +41,8 @@
 // hiQ*loK, loQ*hiK, loQ*loK for the scores; one FP32 accumulator, the B
 // fragment as the MFMA's first source, the K tail zero-filled), so results
 // are bitwise equal to theirs.
+#include <type_traits>
+
 #include "heal.h"
 #include "heal_device.h"
 #include "heal_internal.h"
@@ -79,8 +90,8 @@ constexpr uint32_t kOOB = 0x80000000u;  // beyond every buffer range: loads read
 #ifndef HEAL_PANEL_STORE_AUX
 #define HEAL_PANEL_STORE_AUX 2
 #endif
-#ifndef HEAL_PANEL_LINES
-#define HEAL_PANEL_LINES 1
+#ifndef HEAL_PANEL_RAG_AUX
+#define HEAL_PANEL_RAG_AUX 0
 #endif
 
 struct PanelArgs {
@@ -156,8 +167,9 @@ __device__ __forceinline__ void split8(const u32x4 *raw, u32x4 &h, u32x4 &l)
 // KC: 32-deep chunks of K (K <= 32 KC).  SCALE: multiply the bf16x3 result
 // by alpha.  PD: steps of B loads in flight per wave.  PBM: rows of the
 // panel (128: two workgroups per CU; 256: one, B read from L2 half as often).
-template <bool SCORES, bool SCALE, int KC, int PD, int PBM>
-__global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(PanelArgs p)
+// RAG: rows of C that are not whole 128-byte lines apart, or N % 4 != 0.
+template <bool SCORES, bool SCALE, int KC, int PD, int PBM, bool RAG>
+__global__ void __launch_bounds__(PNT, PBM <= 64 ? (SCORES ? 3 : 2) : PBM <= 128 ? 2 : 1) gemm_panel_kernel(PanelArgs p)
 {
     constexpr int PRB = PBM / 16;               // 16-row blocks of the panel
     constexpr int PPLANE = PBM * PRP;           // one LDS plane of the panel
@@ -165,10 +177,16 @@ __global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(Pan
     constexpr int ES = SCORES ? 2 : 4;          // bytes per operand element
     constexpr int RQ = SCORES ? 1 : 2;          // 16-byte loads per 8 values
     constexpr int UPR = 32 * KC * ES / 16;      // 16-byte units per panel row
-    constexpr int PU = PBM * UPR / PNT;         // panel units per thread
-    static_assert(PU * PNT == PBM * UPR, "whole panel units per thread");
+    constexpr int PU = (PBM * UPR + PNT - 1) / PNT;   // panel units per thread
+    constexpr bool PART = PBM * UPR % PNT != 0; // a small panel: the last units are short of threads
 
-    __shared__ __attribute__((aligned(16))) char smem[2 * PPLANE];
+    // Panels of at most 64 rows, bound by reading B: each wave reads its rows
+    // of B in memory order (a fragment's own order touches 16 rows with every
+    // 16 lanes, a line each) and turns them through an LDS area of its own.
+    constexpr bool TURN = PBM <= 64;
+    constexpr int NBU = UPR / 2;                // 16-byte units of B per lane and step
+    constexpr int TURN_BYTES = TURN ? 32 * UPR * 16 : 0;
+    __shared__ __attribute__((aligned(16))) char smem[2 * PPLANE + 4 * TURN_BYTES];
     char *const ph = smem;                      // hi plane
     char *const pl = smem + PPLANE;             // lo plane
 
@@ -200,7 +218,7 @@ __global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(Pan
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
         const int q = tid + PNT * u, r = q / UPR, c = q % UPR;   // row, 16-byte unit
-        const bool ok = r < rows && (int64_t)c * (16 / ES) < K;
+        const bool ok = r < rows && (int64_t)c * (16 / ES) < K && (!PART || q < PBM * UPR);
         pa[u] = bload(ra, ok ? (uint32_t)((r * p.lda) * ES + c * 16) : kOOB);
     }
 
@@ -214,15 +232,36 @@ __global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(Pan
     // at one time then write to many column ranges of C rather than all to
     // the same 512 bytes of every row (attention scores: bf16x3 1.2x, INT16
     // 1.07x faster).  The order of the steps changes no result.
-    const int cnt = s_end - s_begin;
+    // the step across the end of a row of C whose length is not whole quads
+    // comes last, with its own stores
+    const bool edge = RAG && N % 4 != 0 && s_end == all_steps;
+    const int cnt = s_end - s_begin - (edge ? 1 : 0);
     const int rot = cnt > 0 ? (int)(pid % cnt) : 0;
     auto step_of = [&](int t) {
         const int u = t + rot;
         return s_begin + (u >= cnt ? u - cnt : u);
     };
-    u32x4 raw[PD][2][KC][RQ];
+    u32x4 raw[TURN ? 1 : PD][2][KC][RQ];
+    u32x4 line[TURN ? PD : 1][NBU];             // B in memory order
+    char *const turn = smem + 2 * PPLANE + wave * TURN_BYTES;
+    // unit c of row r of the area, rotated so that the 16 rows of a fragment
+    // read fall in different bank groups
+    auto turn_off = [](int r, int c) {
+        const int x = c + r % UPR;
+        return (r * UPR + (x >= UPR ? x - UPR : x)) * 16;
+    };
     auto clamp = [&](int t) { return t < cnt ? t : (cnt > 0 ? cnt - 1 : 0); };
     auto load_b = [&](int set, int s) {
+        if constexpr (TURN) {
+#pragma unroll
+            for (int u = 0; u < NBU; ++u) {
+                const int q = u * 64 + lane, r = q / UPR, c = q % UPR;
+                const int64_t n = (int64_t)s * PBN + wave * PWN + r;
+                const bool ok = n < N && (int64_t)c * (16 / ES) < K;
+                line[set][u] = bload(rb, ok ? (uint32_t)((n * p.ldb) * ES + c * 16) : kOOB);
+            }
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int64_t n = (int64_t)s * PBN + wave * PWN + j * 16 + fr;
@@ -248,6 +287,7 @@ __global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(Pan
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
         const int q = tid + PNT * u, r = q / UPR, c = q % UPR;
+        if (PART && q >= PBM * UPR) break;
         if constexpr (SCORES) {
             u32x4 h, l;
             split8<true>(&pa[u], h, l);
@@ -281,21 +321,38 @@ __global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(Pan
     // steps (register sets are compile-time choices and every wait stays
     // exact); a step past the last one multiplies clamped copies and stores
     // nothing.
-    auto step = [&](int set, int t) {
-        const bool live = t < cnt;
-        const int s = step_of(clamp(t));
+    auto step = [&](int set, int t, auto edge_tag) {
+        constexpr bool EDGE = decltype(edge_tag)::value;
+        const bool live = EDGE || t < cnt;
+        const int s = EDGE ? (int)all_steps - 1 : step_of(clamp(t));
         u32x4 bh[2][KC], bl[2][KC];
+        if constexpr (TURN) {
+            // (a wave's LDS accesses are served in order: no barrier)
+#pragma unroll
+            for (int u = 0; u < NBU; ++u) {
+                const int q = u * 64 + lane, r = q / UPR, c = q % UPR;
+                *reinterpret_cast<u32x4 *>(turn + turn_off(r, c)) = line[set][u];
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int c = 0; c < KC; ++c)
+#pragma unroll
+                    for (int h = 0; h < RQ; ++h)
+                        raw[0][j][c][h] = *reinterpret_cast<const u32x4 *>(
+                            turn + turn_off(16 * j + fr, (4 * c + fg) * RQ + h));
+        }
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int c = 0; c < KC; ++c) split8<SCORES>(raw[set][j][c], bh[j][c], bl[j][c]);
+            for (int c = 0; c < KC; ++c) split8<SCORES>(raw[TURN ? 0 : set][j][c], bh[j][c], bl[j][c]);
         // The reload goes into the registers just split (steps past the end
         // reload the last step: loads whose data is never used), after the
         // split: the scheduling barriers keep the compiler from hoisting
         // them into another register set, which it then copies back with a
         // wait for every outstanding store.
         __builtin_amdgcn_sched_barrier(0);
-        load_b(set, step_of(clamp(t + PD)));
+        if (!EDGE) load_b(set, step_of(clamp(t + PD)));
         __builtin_amdgcn_sched_barrier(0);
 
         // Row blocks one after another: the panel fragments of block i + 1
@@ -319,7 +376,6 @@ __global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(Pan
         for (int i = 0; i < PRB; ++i) {
             u32x4 nh[KC], nl[KC];
             if (i + 1 < PRB) read_a(i + 1, nh, nl);
-#if HEAL_PANEL_LINES
             // both 16 x 16 results of the row block, then whole 128-byte
             // lines per store: one store holds rows 0..7 of the block, 32
             // columns each, the other rows 8..15
@@ -342,38 +398,25 @@ __global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(Pan
             {
                 const int64_t mx = m0 + 16 * i + (fr & 7), my = mx + 8;
                 const int64_t n = (int64_t)s * PBN + wave * PWN + 16 * (fr >> 3) + 4 * fg;
-                const uint32_t ox = live && mx < M && n < N ? (uint32_t)((mx * p.ldc + n) * 4) : kOOB;
-                const uint32_t oy = live && my < M && n < N ? (uint32_t)((my * p.ldc + n) * 4) : kOOB;
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rc, (int)ox, 0,
-                                                       HEAL_PANEL_STORE_AUX);
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, y), rc, (int)oy, 0,
-                                                       HEAL_PANEL_STORE_AUX);
-            }
-#else
-            const int64_t m = m0 + 16 * i + fr;
+                const int64_t last = EDGE ? N - 4 : N - 1;   // last column a whole quad starts at
+                const uint32_t ox = live && mx < M && n <= last ? (uint32_t)((mx * p.ldc + n) * 4) : kOOB;
+                const uint32_t oy = live && my < M && n <= last ? (uint32_t)((my * p.ldc + n) * 4) : kOOB;
+                constexpr int AUX = RAG ? HEAL_PANEL_RAG_AUX : HEAL_PANEL_STORE_AUX;
+                const u32x4 xv = __builtin_bit_cast(u32x4, x), yv = __builtin_bit_cast(u32x4, y);
+                __builtin_amdgcn_raw_buffer_store_b128(xv, rc, (int)ox, 0, AUX);
+                __builtin_amdgcn_raw_buffer_store_b128(yv, rc, (int)oy, 0, AUX);
+                if constexpr (EDGE) {
+                    // the one to three columns past the last whole quad
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int c = 0; c < KC; ++c) {
-                    a = mma<SCORES>(bh[j][c], ah[c], a);
-                    a = mma<SCORES>(bl[j][c], ah[c], a);
-                    a = mma<SCORES>(bh[j][c], al[c], a);
-                    if constexpr (SCORES) a = mma<SCORES>(bl[j][c], al[c], a);
+                    for (int e = 0; e < 3; ++e) {
+                        const bool in = n > last && n + e < N;
+                        const uint32_t ex = in && mx < M ? (uint32_t)((mx * p.ldc + n + e) * 4) : kOOB;
+                        const uint32_t ey = in && my < M ? (uint32_t)((my * p.ldc + n + e) * 4) : kOOB;
+                        __builtin_amdgcn_raw_buffer_store_b32(xv[e], rc, (int)ex, 0, AUX);
+                        __builtin_amdgcn_raw_buffer_store_b32(yv[e], rc, (int)ey, 0, AUX);
+                    }
                 }
-                // FP32 C, no downcast
-                if (SCORES || SCALE) a = a * scale;
-                const int64_t n = (int64_t)s * PBN + wave * PWN + j * 16 + 4 * fg;
-                // buffer store, lanes outside C (and every lane of a step
-                // past the end) at an offset beyond its range: no branch
-                // around the store, so that each wait for a reload counts the
-                // stores exactly and does not wait for them
-                const uint32_t off =
-                    live && m < M && n < N ? (uint32_t)((m * p.ldc + n) * 4) : kOOB;
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a), rc, (int)off, 0,
-                                                       HEAL_PANEL_STORE_AUX);
             }
-#endif
             if (i + 1 < PRB) {
 #pragma unroll
                 for (int c = 0; c < KC; ++c) {
@@ -386,52 +429,121 @@ __global__ void __launch_bounds__(PNT, PBM <= 128 ? 2 : 1) gemm_panel_kernel(Pan
     };
     for (int t0 = 0; t0 < cnt; t0 += PD) {
 #pragma unroll
-        for (int d = 0; d < PD; ++d) step(d, t0 + d);
+        for (int d = 0; d < PD; ++d) step(d, t0 + d, std::false_type{});
+    }
+    if constexpr (RAG) {
+        if (edge) {
+            load_b(0, (int)all_steps - 1);
+            step(0, 0, std::true_type{});
+        }
     }
 }
 
-template <bool SCORES, bool SCALE>
+template <bool SCORES, bool SCALE, int PBM, bool RAG>
 hipError_t launch_kc(const PanelArgs &a, hipStream_t stream)
 {
     constexpr int PD = SCORES ? HEAL_PANEL_PD_SCORES : HEAL_PANEL_PD;
-    constexpr int BM = SCORES ? HEAL_PANEL_BM_SCORES : HEAL_PANEL_BM;
-    const dim3 grid((unsigned)(a.batch * ((a.M + BM - 1) / BM) * a.csplit));
+    const dim3 grid((unsigned)(a.batch * ((a.M + PBM - 1) / PBM) * a.csplit));
     const int kc = (int)((a.K + 31) / 32);
     switch (kc) {
-    case 1: hipLaunchKernelGGL((gemm_panel_kernel<SCORES, SCALE, 1, PD, BM>), grid, dim3(PNT), 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((gemm_panel_kernel<SCORES, SCALE, 2, PD, BM>), grid, dim3(PNT), 0, stream, a); break;
-    case 3: hipLaunchKernelGGL((gemm_panel_kernel<SCORES, SCALE, 3, PD, BM>), grid, dim3(PNT), 0, stream, a); break;
-    case 4: hipLaunchKernelGGL((gemm_panel_kernel<SCORES, SCALE, 4, PD, BM>), grid, dim3(PNT), 0, stream, a); break;
+    case 1: hipLaunchKernelGGL((gemm_panel_kernel<SCORES, SCALE, 1, PD, PBM, RAG>), grid, dim3(PNT), 0, stream, a); break;
+    case 2: hipLaunchKernelGGL((gemm_panel_kernel<SCORES, SCALE, 2, PD, PBM, RAG>), grid, dim3(PNT), 0, stream, a); break;
+    case 3: hipLaunchKernelGGL((gemm_panel_kernel<SCORES, SCALE, 3, PD, PBM, RAG>), grid, dim3(PNT), 0, stream, a); break;
+    case 4: hipLaunchKernelGGL((gemm_panel_kernel<SCORES, SCALE, 4, PD, PBM, RAG>), grid, dim3(PNT), 0, stream, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
+// Rows of the panel of an output of M rows: 256 (bf16x3) or 128 (scores) where
+// there are that many, else the smallest that holds them.
+int panel_rows(int64_t M, bool scores)
+{
+    const int most = scores ? HEAL_PANEL_BM_SCORES : HEAL_PANEL_BM;
+    if (M > 64) return M > 128 ? most : 128;
+    return M > 32 ? 64 : M > 16 ? 32 : 16;
+}
+
+// Workgroups per panel, each walking its share of the columns.  Panels of at
+// most 64 rows only read B: as many workgroups as there are steps, up to eight
+// per CU in all (64 heads of 4 x 16384 x 128 INT16 54.9 us, 66.9 with half).
+// Larger ones: at least two (above), and as many as make the fewest rounds
+// of workgroups times the length of one, its columns in steps and one more step
+// for its panel (8 heads of 2048 x 2048 x 128 bf16x3 56.4 us with two per panel,
+// 38.9 with four; 32 heads of 1531 x 1531 x 128 INT16 128 with two, 115 with
+// four).
+int panel_csplit(int64_t M, int64_t N, int64_t batch, int PBM)
+{
+    const int64_t panels = batch * ((M + PBM - 1) / PBM), steps = (N + PBN - 1) / PBN;
+    const int64_t cus = device_cus();
+    if (PBM <= 64) {
+        const int64_t c = (8 * cus + panels - 1) / panels;
+        return (int)(c < steps ? c : steps);
+    }
+    const int64_t slots = PBM > 128 ? cus : 2 * cus;
+    int best = 1;
+    float least = 0.0f;
+    for (int c = steps < HEAL_PANEL_CSPLIT ? (int)steps : HEAL_PANEL_CSPLIT; c <= steps && c <= 32; ++c) {
+        const float cost = (float)((panels * c + slots - 1) / slots) * ((float)steps / (float)c + 1.0f);
+        if (least == 0.0f || cost < least) {
+            least = cost;
+            best = c;
+        }
+    }
+    return best;
+}
+
+template <bool SCORES, bool SCALE>
+hipError_t launch_panel(PanelArgs a, hipStream_t stream)
+{
+    // whole lines of C are streamed past the caches; rows of other lengths
+    // leave half lines, which have to meet in L2
+    const bool rag = a.N % 4 != 0 || a.ldc % 32 != 0 || a.strideC % 32 != 0 ||
+                     (reinterpret_cast<uintptr_t>(a.C) & 127u) != 0;
+    const int pbm = panel_rows(a.M, SCORES);
+    a.csplit = panel_csplit(a.M, a.N, a.batch, pbm);
+    switch (pbm) {
+    case 16: return rag ? launch_kc<SCORES, SCALE, 16, true>(a, stream) : launch_kc<SCORES, SCALE, 16, false>(a, stream);
+    case 32: return rag ? launch_kc<SCORES, SCALE, 32, true>(a, stream) : launch_kc<SCORES, SCALE, 32, false>(a, stream);
+    case 64: return rag ? launch_kc<SCORES, SCALE, 64, true>(a, stream) : launch_kc<SCORES, SCALE, 64, false>(a, stream);
+    case 128: return rag ? launch_kc<SCORES, SCALE, 128, true>(a, stream) : launch_kc<SCORES, SCALE, 128, false>(a, stream);
+    case 256:
+        if constexpr (!SCORES || HEAL_PANEL_BM_SCORES == 256)
+            return rag ? launch_kc<SCORES, SCALE, 256, true>(a, stream) : launch_kc<SCORES, SCALE, 256, false>(a, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
 // Shape conditions shared by both products (es: bytes per operand element).
 // K at most 128 and nonzero, whole 16-byte units along K (quads of FP32,
-// eights of INT16), 16-byte rows of A, B and C, N % 4 == 0 (whole 16-byte
-// stores), at least one full panel of rows, every byte offset a lane may
+// eights of INT16), 16-byte rows of A and B, every byte offset a lane may
 // address within a panel of A or a batch entry of B below 2^31, and one
-// workgroup per (batch entry, panel) within the grid limit; C written with
-// buffer stores, so a batch entry of C spans less than 2^31 bytes.
+// workgroup per (batch entry, panel, step) within the grid limit; C written
+// with buffer stores, so a batch entry of C spans less than 2^31 bytes.  The
+// rows of C may have any length and alignment.
 bool panel_shape_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
-                    int64_t batch, int es, int PBM, int csplit)
+                    int64_t batch, int es)
 {
-    if (K <= 0 || K > PKMAX || (K * es) % 16 != 0 || N % 4 != 0 || M < PBM) return false;
+    if (K <= 0 || K > PKMAX || (K * es) % 16 != 0 || N < 4) return false;
     const int64_t lim = 0x7fffffffLL;
-    if (((int64_t)(PBM - 1) * lda + K) * es >= lim) return false;
+    if (((int64_t)255 * lda + K) * es >= lim) return false;
     if (((N - 1) * ldb + K) * es >= lim) return false;
     if (((M - 1) * ldc + N) * 4 >= lim) return false;
-    return batch * ((M + PBM - 1) / PBM) * csplit <= lim;
+    // 2^21 16 x 16 blocks at most per launch: the grid stays below 2^31
+    return batch * ((M + 15) / 16) * ((N + PBN - 1) / PBN) <= lim;
 }
 
 }  // namespace
 
 bool panel_kernel_applies(const GemmArgs &a, bool trans_b)
 {
-    return trans_b && a.vecA && a.vecB && a.vecC &&
-           panel_shape_ok(a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.batch, 4, HEAL_PANEL_BM,
-                          HEAL_PANEL_CSPLIT);
+    // Up to 64 rows the skinny kernels stay for narrow outputs, and their generic
+    // tiles for up to 16 rows where N is not whole quads (one head of 16 x 16 x
+    // 128 3.8 us against 5.4; 32 heads of 1 x 3001 x 128 10.7 against 14.3; but
+    // 64 heads of 4 x 16384 x 128 168 against 99, 32 of 50 x 50 x 64 6.9 against 5.1).
+    if (a.M <= 64 && (a.N % 4 == 0 ? a.N < 256 : a.M <= 16)) return false;
+    return trans_b && a.vecA && a.vecB &&
+           panel_shape_ok(a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.batch, 4);
 }
 
 hipError_t launch_gemm_panel(const GemmArgs &g, bool use_alpha, hipStream_t stream)
@@ -451,14 +563,12 @@ hipError_t launch_gemm_panel(const GemmArgs &g, bool use_alpha, hipStream_t stre
     a.strideC = g.strideC;
     a.batch = g.batch;
     a.alpha = g.alpha;
-    a.csplit = HEAL_PANEL_CSPLIT;
-    return use_alpha ? launch_kc<false, true>(a, stream) : launch_kc<false, false>(a, stream);
+    return use_alpha ? launch_panel<false, true>(a, stream) : launch_panel<false, false>(a, stream);
 }
 
 bool scores_panel_applies(const OpArgs &a)
 {
-    return a.vecA && a.vecB && a.vecC && panel_shape_ok(a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.batch, 2,
-                                                     HEAL_PANEL_BM_SCORES, HEAL_PANEL_CSPLIT);
+    return a.vecA && a.vecB && panel_shape_ok(a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.batch, 2);
 }
 
 hipError_t launch_scores_panel(const OpArgs &o, hipStream_t stream)
@@ -480,8 +590,7 @@ hipError_t launch_scores_panel(const OpArgs &o, hipStream_t stream)
     a.alpha = o.alpha;
     a.maxA = o.maxA;
     a.maxB = o.maxB;
-    a.csplit = HEAL_PANEL_CSPLIT;
-    return launch_kc<true, false>(a, stream);
+    return launch_panel<true, false>(a, stream);
 }
 
 }  // namespace heal

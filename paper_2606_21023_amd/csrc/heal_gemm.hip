@@ -616,25 +616,25 @@ hipError_t launch_gemm(int instance, const GemmArgs &a, bool trans_b, bool use_a
     if (instance == HEAL_INSTANCE_AUTO) {
         if (HEAL_PANEL && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
         instance = select_instance(a.M, a.N);
-        if (instance != HEAL_INSTANCE_SKINNY) {
-            DirectArgs d = {};
-            d.M = a.M;
-            d.N = a.N;
-            d.K = a.K;
-            d.A = a.A;
-            d.lda = a.lda;
-            d.strideA = a.strideA;
-            d.B = a.B;
-            d.ldb = a.ldb;
-            d.strideB = a.strideB;
-            d.C = a.C;
-            d.ldc = a.ldc;
-            d.strideC = a.strideC;
-            d.batch = a.batch;
-            d.alpha = a.alpha;
-            const int cfg = direct_plan(OP_BF16X3, trans_b, d);
-            if (cfg >= 0) return launch_direct(OP_BF16X3, trans_b, cfg, d, stream);
-        }
+        DirectArgs d = {};
+        d.M = a.M;
+        d.N = a.N;
+        d.K = a.K;
+        d.A = a.A;
+        d.lda = a.lda;
+        d.strideA = a.strideA;
+        d.B = a.B;
+        d.ldb = a.ldb;
+        d.strideB = a.strideB;
+        d.C = a.C;
+        d.ldc = a.ldc;
+        d.strideC = a.strideC;
+        d.batch = a.batch;
+        d.alpha = a.alpha;
+        d.vec = a.vecA && a.vecB && a.K % 4 == 0 && (trans_b || a.N % 4 == 0);
+        const int plan = direct_plan(OP_BF16X3, trans_b, d);
+        if (plan >= 0) return launch_direct(OP_BF16X3, trans_b, plan, d, stream);
+        if (plan == DIRECT_MEDIUM) instance = HEAL_INSTANCE_MEDIUM;
     }
     switch (instance) {
     case HEAL_INSTANCE_LARGE:

@@ -228,6 +228,17 @@ gemm_direct_kernel(DirectArgs p)
 #pragma unroll
         for (int u = 0; u < NA; ++u)
             va[u] = a_row[u] < rows ? (uint32_t)((a_row[u] * p.lda + 4 * a_kq[u]) * 4) : kOOB;
+        // with a K tail: the last stage's offsets, past the end of K beyond the
+        // buffer and a quad across it back_k elements early
+        uint32_t vat[TAIL ? NA : 1];
+        if constexpr (TAIL) {
+#pragma unroll
+            for (int u = 0; u < NA; ++u) {
+                const int k = (ns - 1) * BK + 4 * a_kq[u];
+                vat[u] = k >= K || a_row[u] >= rows
+                             ? kOOB : va[u] + (ns - 1) * BK * 4 - (k + 4 > K ? 4u * back_k : 0u);
+            }
+        }
         uint32_t vb[NB];
         // B_COLS: a lane's NB columns are NB*fr .. +NB-1 of the wave's; the lane
         // whose columns cross the edge of B reads them back_n early
@@ -259,12 +270,9 @@ gemm_direct_kernel(DirectArgs p)
             const int so = (s < ns ? s : ns - 1) * BK * 4;
 #pragma unroll
             for (int u = 0; u < NA; ++u) {
-                uint32_t v = va[u] | past;
-                if (TAIL) {
-                    const int k = s * BK + 4 * a_kq[u];
-                    v = k >= K || (v & kOOB) ? kOOB : v + so - (k + 4 > K ? 4u * back_k : 0u);
-                }
-                ra[u] = bload4(r, v, TAIL ? 0 : so);
+                uint32_t v = va[u];
+                if (TAIL) v = s >= ns - 1 ? vat[u] : v + so;
+                ra[u] = bload4(r, v | past, TAIL ? 0 : so);
             }
         };
         auto load_b = [&](u32x4 (*rb)[RB], int c) {
@@ -277,8 +285,8 @@ gemm_direct_kernel(DirectArgs p)
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     const int so = (kc * 32 + t) * (int)p.ldb * 4;
-                    uint32_t w = o;
-                    if (TAIL) w = kc * 32 + 8 * fg + t >= K || (o & kOOB) ? kOOB : o + so;
+                    // rows past K start past the end of the buffer
+                    const uint32_t w = TAIL ? o + so : o;
                     bload_v<NB>(r, w, TAIL ? 0 : so, v + t * NB);
                 }
             } else {
@@ -540,26 +548,39 @@ gemm_direct_kernel(DirectArgs p)
                 }
             }
         };
+        // pairs of 16-column blocks as whole 128-byte lines (whole_lines)
+        constexpr int LN = BS == B_COLS ? 0 : NB / 2 * 2;
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
-            const int64_t m = m0 + (wm * MB + i) * 16 + fr;
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
+            const int64_t mb = m0 + (wm * MB + i) * 16;
+            const int64_t nb = n0 + wn * 16 * NB;
+            auto block = [&](int j) {
                 f32x4 v;
-                int64_t n = n0 + wn * 16 * NB;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[t] = scaled(acc[j][i][t]);
+                return v;
+            };
+#pragma unroll
+            for (int j = 0; j < LN; j += 2) {
+                f32x4 x, y;
+                whole_lines(block(j), block(j + 1), fr, x, y);
+                const int64_t n = nb + 16 * j + 16 * (fr >> 3) + 4 * fg;
+                store_c(mb + (fr & 7), n, x);
+                store_c(mb + 8 + (fr & 7), n, y);
+            }
+#pragma unroll
+            for (int j = LN; j < NB; ++j) {
                 if constexpr (BS == B_COLS) {
                     // the lane's 4 NB results are columns 4 NB fg .. of the wave's,
                     // result e of block c at NB e + c
+                    f32x4 v;
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
                         v[t] = scaled(acc[(4 * j + t) % NB][i][(4 * j + t) / NB]);
-                    n += 4 * NB * fg + 4 * j;
+                    store_c(mb + fr, nb + 4 * NB * fg + 4 * j, v);
                 } else {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) v[t] = scaled(acc[j][i][t]);
-                    n += 16 * j + 4 * fg;
+                    store_c(mb + fr, nb + 16 * j + 4 * fg, block(j));
                 }
-                store_c(m, n, v);
             }
         }
         if (b + gridDim.y < p.batch) __syncthreads();  // LDS reuse by the next batch entry
@@ -595,7 +616,9 @@ hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
     //                                      MB WVM NB WVN KS RC LW RA PIPE
     case T32x32: return launch_cfg<OP, BS, 2, 1, 1, 2, 2, 4, 2, 2, true>(a, stream);
     case T32x64: return launch_cfg<OP, BS, 2, 1, 1, 4, 2, 4, 4, 2, true>(a, stream);
-    case T64x128: return launch_cfg<OP, BS, 4, 1, 2, 4, 2, 4, 4, 4, true>(a, stream);
+    case T64x128:
+        if constexpr (PACKED) return launch_cfg<OP, BS, 4, 1, 2, 4, 2, 4, 4, 4, true>(a, stream);
+        else return launch_cfg<OP, BS, 4, 1, 2, 4, 2, 2, 4, 2, true>(a, stream);
     case T128x128: return launch_cfg<OP, BS, 8, 1, 2, 4, 2, 2, 4, 2, false>(a, stream);
     case T96x128:
         if constexpr (PACKED) return launch_cfg<OP, BS, 6, 1, 2, 4, 2, 4, 4, 4, false>(a, stream);
@@ -613,40 +636,69 @@ hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
     return hipErrorInvalidValue;
 }
 
-// Time of one launch by configuration: us at 4096 deep with 64 tiles, with 256
-// (one per CU), and per further 256 tiles (0: one tile per CU at a time, so
-// whole rounds).  Measured on 128 to 3072 x 4096 x 4096 products; the last row
-// is the 256 x 256 tiles of the large kernels.  Other depths scale all alike.
-// The smallest of these estimates picks the tile; 0 in the middle: not built.
-struct Cost { float few, full, more; };
-constexpr Cost kCost[5][T_COUNT + 1] = {
-    // 32x32            32x64               32x128              64x64            64x128
-    // 96x128           128x128             128x256             large
+// Time of one launch by kernel: us at 4096 deep with 64 tiles, with 256 (one
+// per CU) and per further 256 tiles (0: one tile per CU at a time, so whole
+// rounds), and a fixed part per 256 tiles (the first loads and C).  Measured
+// on 128 to 3072 x 4096 x 4096 products and on products 64 to 512 deep; the last
+// two are the 128 x 128 and the 256 x 256 tiles of the staged kernels.  The
+// smallest of these estimates picks the tile; 0: not built.
+constexpr int kMedium = T_COUNT, kLarge = T_COUNT + 1;
+struct Cost { float few, full, more, fixed; };
+constexpr Cost kCost[5][T_COUNT + 2] = {
+    // 32x32, 32x64, 32x128, 64x64; 64x128, 96x128, 128x128, 128x256; medium, large
     /* HEAL-Base */
-    {{13, 15, 7.5f}, {14, 17.6f, 11}, {17.5f, 19.4f, 16}, {0, 0, 0}, {23.1f, 28, 0},
-     {29, 38.4f, 0}, {39.5f, 50.6f, 0}, {0, 0, 0}, {82, 122, 0}},
+    {{13, 15, 7.5f, 0.8f}, {14, 17.6f, 11, 1.1f}, {17.5f, 19.4f, 16, 1.6f}, {0, 0, 0, 0},
+     {23.1f, 28, 0, 3}, {29, 38.4f, 0, 4}, {39.5f, 50.6f, 0, 5}, {0, 0, 0, 0},
+     {42, 53.7f, 0, 2}, {82, 122, 0, 13}},
     /* HEAL-Full */
-    {{15, 18.5f, 8.8f}, {16, 21, 13.3f}, {19.8f, 25.6f, 21}, {0, 0, 0}, {29.9f, 40.4f, 0},
-     {43.3f, 57.5f, 0}, {57, 74.5f, 0}, {93, 134, 0}, {150, 216, 0}},
+    {{15, 18.5f, 8.8f, 0.8f}, {16, 21, 13.3f, 1.1f}, {19.8f, 25.6f, 21, 1.6f}, {0, 0, 0, 0},
+     {29.9f, 40.4f, 0, 3}, {43.3f, 57.5f, 0, 4}, {57, 74.5f, 0, 5}, {93, 134, 0, 11},
+     {72.5f, 85.6f, 0, 2}, {150, 216, 0, 13}},
     /* (INT16 scores: not here) */
     {},
     /* pre-split */
-    {{17, 20, 11.5f}, {18, 22.2f, 17.5f}, {27.3f, 31.8f, 30}, {0, 0, 0}, {37.6f, 49.5f, 0},
-     {53.2f, 74, 0}, {64.7f, 92.7f, 0}, {0, 0, 0}, {185, 273, 0}},
+    {{17, 20, 11.5f, 0.8f}, {18, 22.2f, 17.5f, 1.1f}, {27.3f, 31.8f, 30, 1.8f}, {0, 0, 0, 0},
+     {37.6f, 49.5f, 0, 3}, {53.2f, 74, 0, 4}, {64.7f, 92.7f, 0, 5}, {0, 0, 0, 0},
+     {91.5f, 104.4f, 0, 2}, {185, 273, 0, 13}},
     /* bf16x3, B stored K x N (N x K below) */
-    {{24, 28, 14}, {27, 31.7f, 23}, {0, 0, 0}, {36, 40.6f, 40}, {61.3f, 66.3f, 0},
-     {66, 83.7f, 0}, {76.9f, 107.3f, 0}, {0, 0, 0}, {200, 283, 0}},
+    {{24, 28, 14, 0.8f}, {27, 31.7f, 23, 1.3f}, {0, 0, 0, 0}, {36, 40.6f, 40, 3.5f},
+     {61.3f, 66.3f, 0, 4}, {66, 83.7f, 0, 4}, {76.9f, 107.3f, 0, 6.2f}, {0, 0, 0, 0},
+     {83.5f, 110, 0, 5.5f}, {200, 283, 0, 15}},
 };
-constexpr Cost kCostRows[T_COUNT + 1] = {
-    {28, 32, 18}, {30, 35, 32}, {0, 0, 0}, {39, 41.9f, 41}, {68, 70.5f, 0},
-    {72, 87.8f, 0}, {81, 111, 0}, {0, 0, 0}, {200, 283, 0}};
+constexpr Cost kCostRows[T_COUNT + 2] = {
+    {28, 32, 18, 0.8f}, {30, 35, 32, 1.3f}, {0, 0, 0, 0}, {39, 41.9f, 41, 3.5f},
+    {68, 70.5f, 0, 4}, {72, 87.8f, 0, 4}, {81, 111, 0, 5.5f}, {0, 0, 0, 0},
+    {87, 113.7f, 0, 5.5f}, {200, 283, 0, 15}};
 
-float estimate(const Cost &c, int64_t tiles, int cus)
+float estimate(const Cost &c, int64_t tiles, int64_t K, int cus)
 {
-    const float r = (float)tiles / (float)cus;
-    if (r <= 1.0f) return c.few + (c.full - c.few) * (r < 0.25f ? 0.0f : (r - 0.25f) / 0.75f);
-    if (c.more > 0.0f) return c.full + (r - 1.0f) * c.more;
-    return c.full * (float)((tiles + cus - 1) / cus);
+    const float r = (float)tiles / (float)cus, depth = (float)K / 4096.0f;
+    const float rounds = (float)((tiles + cus - 1) / cus);
+    if (r <= 1.0f)
+        return c.fixed + depth * (c.few + (c.full - c.few) * (r < 0.25f ? 0.0f : (r - 0.25f) / 0.75f));
+    if (c.more > 0.0f) return c.fixed * r + depth * (c.full + (r - 1.0f) * c.more);
+    return c.fixed * rounds + depth * c.full * rounds;
+}
+
+// Up to 64 rows the skinny kernels stream B; the direct-B kernel is faster where
+// their narrow strips each convert all of A.  64 x N x 4096, us, skinny ->
+// direct: HEAL-Full 1024 columns 28.5 -> 19.1, 4096 30.9 -> 19.2, 8192 42.0 -> 20.2,
+// 14336 56.2 -> 35.7, 65536 145 -> 112, 128256 208 -> 225; HEAL-Base 8192 25.9 ->
+// 17.8, 16032 38.6 -> 36.4, 32064 53.2 -> 54.6, 65536 131 -> 103, 128256 201 -> 214;
+// pre-split 8192 49.0 -> 34.7, 14336 64.8 -> 57.6, 16032 58.2 -> 59.8, 65536 215 ->
+// 197; K x N 4096 23.3 -> 28.6, 8192 41.9 -> 40.2, 16032 66.8 -> 57.7, 32064 113 -> 94;
+// N x K 8192 40.3 -> 43.5, 14336 72.0 -> 58.2, 32064 109 -> 117.  32 rows: HEAL-Full
+// 4096 16.8 -> 19.1, 8192 24.1 -> 19.6, 16032 39.2 -> 34.6, 32064 55.0 -> 50.7;
+// pre-split 8192 28.1 -> 29.4, 16032 54.2 -> 48.8.
+bool beats_skinny(int op, bool rows, const DirectArgs &a)
+{
+    if (a.batch != 1 || a.K < 256 || a.M <= 16) return false;
+    const int64_t N = a.N;
+    if (op == OP_BF16X3)
+        return a.M > 32 && (rows ? N >= 10240 && N <= 16384 : N >= 8192 && N <= 32768);
+    if (a.M <= 32) return N >= (op == OP_PRESPLIT ? 16000 : 8192) && N <= 32768;
+    if (N >= 15360 && N < 61440 && op != OP_FULL) return false;
+    return N <= 98304;
 }
 
 }  // namespace
@@ -658,30 +710,48 @@ int direct_plan(int op, bool trans_b, const DirectArgs &a)
     // past its end for the clamped index)
     const int64_t lim = 0x7fffffffLL;
     const bool rows = op == OP_BF16X3 && trans_b, cols = op == OP_BF16X3 && !trans_b;
-    if (a.K < 4 || a.K > (1 << 28) || ((int64_t)127 * a.lda + a.K + 128) * 4 >= lim) return -1;
-    if (rows && ((int64_t)255 * a.ldb + a.K + 128) * 4 >= lim) return -1;
-    if (cols && (a.N < 4 || (a.K + 128) * a.ldb * 4 >= lim)) return -1;
+    if (a.K < 4 || a.K > (1 << 28) || ((int64_t)127 * a.lda + a.K + 128) * 4 >= lim)
+        return DIRECT_NONE;
+    if (rows && ((int64_t)255 * a.ldb + a.K + 128) * 4 >= lim) return DIRECT_NONE;
+    if (cols && (a.N < 4 || (a.K + 128) * a.ldb * 4 >= lim)) return DIRECT_NONE;
+    // the staged kernels read rows that are not whole 16-byte units by element
+    // (16 x 1003 x 999, us: K x N 30.3 -> 9.3, N x K 25.8 -> 12.7, HEAL-Base 8.6 ->
+    // 6.8, pre-split 8.9 -> 8.6, but HEAL-Full 8.5 -> 9.3)
+    if (a.M <= 64 && (a.vec || (a.M <= 16 && op == OP_FULL)) && !beats_skinny(op, rows, a))
+        return DIRECT_NONE;
     const int cus = device_cus();
     const Cost *cost = rows ? kCostRows : kCost[op];
     auto tiles = [&](int64_t bm, int64_t bn) {
         return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.batch;
     };
-    // the large kernels' tiles: a part-empty round costs less than a whole
-    // one (a power-limited chip runs fewer tiles faster)
-    const int64_t nl = tiles(256, 256);
-    float best = estimate(cost[T_COUNT], nl, cus);
-    if (nl > cus) best = 0.5f * (best + cost[T_COUNT].full * (float)nl / (float)cus);
-    int cfg = -1;
+    float best = 0.0f;
+    int plan = DIRECT_NONE;
+    if (a.vec && a.M > 64) {
+        // the large kernels' tiles: a part-empty round costs less than a whole
+        // one (a power-limited chip runs fewer tiles faster)
+        const int64_t nl = tiles(256, 256);
+        best = estimate(cost[kLarge], nl, a.K, cus);
+        if (nl > cus)
+            best = 0.5f * (best + (cost[kLarge].fixed + cost[kLarge].full * (float)a.K / 4096.0f) *
+                                      (float)nl / (float)cus);
+        const float t = estimate(cost[kMedium], tiles(128, 128), a.K, cus);
+        if (t < best) {
+            best = t;
+            plan = DIRECT_MEDIUM;
+        }
+    }
     for (int c = 0; c < T_COUNT; ++c) {
         const int64_t n = tiles(kTileM[c], kTileN[c]);
         if (cost[c].full <= 0.0f || n > (1 << 20)) continue;
-        const float t = estimate(cost[c], n, cus);
-        if (t < best) {
+        // (its K-tail form spills registers)
+        if (c == T128x128 && op == OP_BF16X3 && a.K % 64 != 0) continue;
+        const float t = estimate(cost[c], n, a.K, cus);
+        if (best == 0.0f || t < best) {
             best = t;
-            cfg = c;
+            plan = c;
         }
     }
-    return cfg;
+    return plan;
 }
 
 hipError_t launch_direct(int op, bool trans_b, int cfg, const DirectArgs &a, hipStream_t stream)

@@ -1488,7 +1488,7 @@ hipError_t launch_gemm_op(int op, int instance, const OpArgs &a, hipStream_t str
     if (instance == HEAL_INSTANCE_AUTO) {
         if (HEAL_PANEL && op == OP_SCORES && scores_panel_applies(a)) return launch_scores_panel(a, stream);
         instance = select_instance(a.M, a.N);
-        if (op != OP_SCORES && instance != HEAL_INSTANCE_SKINNY) {
+        if (op != OP_SCORES) {
             DirectArgs d = {};
             d.M = a.M;
             d.N = a.N;
@@ -1500,8 +1500,10 @@ hipError_t launch_gemm_op(int op, int instance, const OpArgs &a, hipStream_t str
             d.ldc = a.ldc;
             d.batch = a.batch;
             d.e = a.e;
-            const int cfg = direct_plan(op, false, d);
-            if (cfg >= 0) return launch_direct(op, false, cfg, d, stream);
+            d.vec = a.vecA && a.K % 4 == 0;
+            const int plan = direct_plan(op, false, d);
+            if (plan >= 0) return launch_direct(op, false, plan, d, stream);
+            if (plan == DIRECT_MEDIUM) instance = HEAL_INSTANCE_MEDIUM;
         }
     }
     switch (op) {

@@ -100,10 +100,14 @@ struct DirectArgs {
     int64_t batch;
     int e;                      // BASE, FULL: C is scaled by 2^-e
     float alpha;                // BF16X3
+    bool vec;                   // the staged kernels can read A and B by 16-byte units
 };
 
-// The tile configuration of the direct-B kernel that a product should take, or
-// -1 where it cannot run the call or the large kernels are faster (host only).
+// The tile configuration (>= 0) of the direct-B kernel that a product should
+// take; DIRECT_MEDIUM where the 128 x 128 staged tiles are faster; DIRECT_NONE
+// where it cannot run the call, or the large or skinny kernels are faster (host
+// only).
+constexpr int DIRECT_NONE = -1, DIRECT_MEDIUM = -2;
 int direct_plan(int op, bool trans_b, const DirectArgs &args);
 hipError_t launch_direct(int op, bool trans_b, int cfg, const DirectArgs &args, hipStream_t stream);
 

@@ -104,3 +104,28 @@ def test_non_finite_rows_stay_apart():
     bad = ~torch.isfinite(C)
     assert bool(bad[69].all()) and bool(bad[:, 44].all())
     assert not bool(bad[:69, :44].any())
+
+
+# up to 64 rows: unaligned sizes of any row count, and the row counts and widths
+# from which the direct-B kernel takes over from the skinny ones
+FEW_ROWS = [(1, 7, 5), (16, 1003, 999), (17, 130, 77), (33, 1024, 256), (64, 4096, 320),
+            (32, 8192, 256), (32, 16000, 260), (33, 15364, 256), (64, 61440, 256),
+            (40, 10240, 512), (64, 8192, 300)]
+
+
+@pytest.mark.parametrize("shape", FEW_ROWS, ids=lambda s: "x".join(map(str, s)))
+def test_few_rows(shape):
+    M, N, K = shape
+    A, W = _rand((M, K), 10), _rand((N, K), 11)
+    W16, Bp = heal.heal_pack_f16_weight(W, 11), heal.heal_presplit_b(W, trans_b=True)
+    B = W.t().contiguous()
+    calls = [("kn", lambda i: heal.heal_gemm_f32_instance(i, A, B)),
+             ("nk", lambda i: heal.heal_gemm_f32_instance(i, A, W, trans_b=True)),
+             ("base", lambda i: heal.heal_gemm_f16w(A, W16, N, 11, 1, instance=i)),
+             ("full", lambda i: heal.heal_gemm_f16w(A, W16, N, 11, 2, instance=i)),
+             ("presplit", lambda i: heal.heal_gemm_f32_presplit(A, Bp, N, instance=i))]
+    for name, call in calls:
+        announce("few rows %s %s" % (name, shape))
+        C, ref = call(heal.INSTANCE_AUTO), call(heal.INSTANCE_SKINNY)
+        torch.cuda.synchronize()
+        _same(C, ref, name)

@@ -26,6 +26,8 @@ Functions (names follow the C ABI):
 import ctypes
 import os
 
+import torch
+
 __all__ = ["HealError", "lib", "library_path", "build_id", "check_build", "heal_split_f32", "heal_gemm_f32",
            "heal_gemm_f32_strided_batched", "heal_gemm_f32_instance", "select_instance",
            "INSTANCE_AUTO", "INSTANCE_LARGE", "INSTANCE_MEDIUM", "INSTANCE_SKINNY", "STATUS",
@@ -134,32 +136,55 @@ def _check(status, what):
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current device's current stream, as a raw pointer.  (The Stream object
+    of torch.cuda.current_stream costs 3 us, a third of a small call.)"""
+    return _raw_stream(_current_device())
 
 
-def _require(t, name, ndim):
-    import torch
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+_f32 = torch.float32
+
+
+def _tensor(t, name, dtype, ndim=None):
+    """Check a CUDA tensor of a type and number of dimensions whose last one is
+    contiguous; returns its shape and strides."""
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise HealError("%s must be a CUDA (HIP) tensor" % name)
-    if t.dtype != torch.float32:
-        raise HealError("%s must be float32, got %s" % (name, t.dtype))
-    if t.dim() != ndim:
-        raise HealError("%s must have %d dimensions, got %d" % (name, ndim, t.dim()))
-    if t.numel() and t.size(-1) > 1 and t.stride(-1) != 1:
+    if t.dtype is not dtype:
+        raise HealError("%s must be %s, got %s" % (name, str(dtype).replace("torch.", ""), t.dtype))
+    shape, stride = t.shape, t.stride()
+    if ndim is not None and len(shape) != ndim:
+        raise HealError("%s must have %d dimensions, got %d" % (name, ndim, len(shape)))
+    if shape and stride[-1] != 1 and shape[-1] > 1 and t.numel():
         # (a last dimension of one element has no stride to respect: torch
         # may report any, e.g. for the transpose of a one-row matrix)
         raise HealError("%s must be contiguous in its last dimension" % name)
+    return shape, stride
 
 
-def _ld(t):
+def _ld(shape, stride):
     """Row stride of the last two dims, in elements."""
-    return t.stride(-2) if t.size(-2) > 1 else max(t.size(-1), 1)
+    return stride[-2] if shape[-2] > 1 else max(shape[-1], 1)
+
+
+def _output(out, like, shape):
+    """`out`, checked, or a new float32 tensor; and its strides."""
+    if out is None:
+        C = like.new_empty(shape)
+        return C, C.stride()
+    got, stride = _tensor(out, "out", _f32, len(shape))
+    if tuple(got) != shape:
+        raise HealError("out has shape %s, expected %s" % (tuple(got), shape))
+    return out, stride
 
 
 def heal_split_f32(x, hi=None, lo=None):
     """Split a contiguous float32 CUDA tensor into bf16 (hi, lo) bit patterns."""
-    import torch
+    return _split("heal_split_f32", x, hi, lo)
+
+
+def _split(what, x, hi, lo):
     if not isinstance(x, torch.Tensor) or not x.is_cuda or x.dtype != torch.float32:
         raise HealError("x must be a float32 CUDA tensor")
     if not x.is_contiguous():
@@ -168,58 +193,47 @@ def heal_split_f32(x, hi=None, lo=None):
         hi = torch.empty(x.shape, dtype=torch.uint16, device=x.device)
     if lo is None:
         lo = torch.empty(x.shape, dtype=torch.uint16, device=x.device)
-    _check(lib().heal_split_f32(x.data_ptr(), hi.data_ptr(), lo.data_ptr(), x.numel(), _stream()),
-           "heal_split_f32")
+    _check(getattr(lib(), what)(x.data_ptr(), hi.data_ptr(), lo.data_ptr(), x.numel(), _stream()),
+           what)
     return hi, lo
 
 
 def heal_gemm_f32(A, B, out=None):
     """C = A @ B (A: M x K, B: K x N, row-major float32 CUDA tensors)."""
-    import torch
-    _require(A, "A", 2)
-    _require(B, "B", 2)
-    M, K = A.shape
-    if B.shape[0] != K:
+    shape_a, stride_a = _tensor(A, "A", _f32, 2)
+    shape_b, stride_b = _tensor(B, "B", _f32, 2)
+    M, K = shape_a
+    N = shape_b[1]
+    if shape_b[0] != K:
         raise HealError("inner dimensions differ: %s @ %s" % (tuple(A.shape), tuple(B.shape)))
-    N = B.shape[1]
-    C = out if out is not None else torch.empty((M, N), dtype=torch.float32, device=A.device)
-    _require(C, "out", 2)
-    if tuple(C.shape) != (M, N):
-        raise HealError("out has shape %s, expected %s" % (tuple(C.shape), (M, N)))
-    _check(lib().heal_gemm_f32(M, N, K, A.data_ptr(), B.data_ptr(), C.data_ptr(),
-                               _ld(A), _ld(B), _ld(C), _stream()), "heal_gemm_f32")
+    C, stride_c = _output(out, A, (M, N))
+    _check((_lib or lib()).heal_gemm_f32(
+        M, N, K, A.data_ptr(), B.data_ptr(), C.data_ptr(), _ld(shape_a, stride_a),
+        _ld(shape_b, stride_b), _ld((M, N), stride_c), _stream()), "heal_gemm_f32")
     return C
 
 
 def _batched(fn_args_prefix, A, B, alpha, trans_b, out, what):
-    import torch
-    _require(A, "A", 3)
-    _require(B, "B", 3)
-    bat, M, K = A.shape
-    if trans_b:
-        N, Kb = B.shape[1], B.shape[2]
-    else:
-        Kb, N = B.shape[1], B.shape[2]
-    if Kb != K or B.shape[0] != bat:
+    shape_a, stride_a = _tensor(A, "A", _f32, 3)
+    shape_b, stride_b = _tensor(B, "B", _f32, 3)
+    bat, M, K = shape_a
+    N, Kb = (shape_b[1], shape_b[2]) if trans_b else (shape_b[2], shape_b[1])
+    if Kb != K or shape_b[0] != bat:
         raise HealError("shapes do not match: A %s, B %s, trans_b=%s"
                         % (tuple(A.shape), tuple(B.shape), trans_b))
-    C = out if out is not None else torch.empty((bat, M, N), dtype=torch.float32, device=A.device)
-    _require(C, "out", 3)
-    if tuple(C.shape) != (bat, M, N):
-        raise HealError("out has shape %s, expected %s" % (tuple(C.shape), (bat, M, N)))
-    sA = A.stride(0) if bat > 1 else 0
-    sB = B.stride(0) if bat > 1 else 0
-    sC = C.stride(0) if bat > 1 else 0
-    st = fn_args_prefix(M, N, K, ctypes.c_float(alpha), A.data_ptr(), _ld(A), sA,
-                        B.data_ptr(), _ld(B), sB, 1 if trans_b else 0,
-                        C.data_ptr(), _ld(C), sC, bat, _stream())
+    C, stride_c = _output(out, A, (bat, M, N))
+    many = bat > 1
+    st = fn_args_prefix(M, N, K, alpha, A.data_ptr(), _ld(shape_a, stride_a),
+                        stride_a[0] if many else 0, B.data_ptr(), _ld(shape_b, stride_b),
+                        stride_b[0] if many else 0, 1 if trans_b else 0, C.data_ptr(),
+                        _ld((M, N), stride_c), stride_c[0] if many else 0, bat, _stream())
     _check(st, what)
     return C
 
 
 def heal_gemm_f32_strided_batched(A, B, alpha=1.0, trans_b=False, out=None):
     """C[b] = alpha * A[b] @ op(B[b]) for 3-D tensors; op(B) = B^T if trans_b."""
-    return _batched(lib().heal_gemm_f32_strided_batched, A, B, alpha, trans_b, out,
+    return _batched((_lib or lib()).heal_gemm_f32_strided_batched, A, B, alpha, trans_b, out,
                     "heal_gemm_f32_strided_batched")
 
 
@@ -236,43 +250,19 @@ def heal_gemm_f32_instance(instance, A, B, alpha=1.0, trans_b=False, out=None):
 
 
 def select_instance(M, N):
-    """The instance heal_gemm_f32 chooses for an M x N output."""
+    """The instance heal_gemm_f32 chooses for an M x N output by its size."""
     return lib().heal_gemm_select_instance(M, N)
 
 
 # ---- FP16 forms, pre-split operand, INT16 scores ---------------------------
 
-def _require_dtype(t, name, dtype, ndim=None):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise HealError("%s must be a CUDA (HIP) tensor" % name)
-    if t.dtype != dtype:
-        raise HealError("%s must be %s, got %s" % (name, dtype, t.dtype))
-    if ndim is not None and t.dim() != ndim:
-        raise HealError("%s must have %d dimensions, got %d" % (name, ndim, t.dim()))
-    if t.numel() and t.size(-1) > 1 and t.stride(-1) != 1:
-        # (a last dimension of one element has no stride to respect: torch
-        # may report any, e.g. for the transpose of a one-row matrix)
-        raise HealError("%s must be contiguous in its last dimension" % name)
-
-
 def heal_split_f16(x, hi=None, lo=None):
     """HEAL-Full pair of a contiguous float32 CUDA tensor, binary16 bit patterns."""
-    import torch
-    _require_dtype(x, "x", torch.float32)
-    if not x.is_contiguous():
-        raise HealError("x must be contiguous")
-    if hi is None:
-        hi = torch.empty(x.shape, dtype=torch.uint16, device=x.device)
-    if lo is None:
-        lo = torch.empty(x.shape, dtype=torch.uint16, device=x.device)
-    _check(lib().heal_split_f16(x.data_ptr(), hi.data_ptr(), lo.data_ptr(), x.numel(), _stream()),
-           "heal_split_f16")
-    return hi, lo
+    return _split("heal_split_f16", x, hi, lo)
 
 
 def heal_packed_size(K, N, planes):
-    n = lib().heal_packed_size(K, N, planes)
+    n = (_lib or lib()).heal_packed_size(K, N, planes)
     if n < 0:
         raise HealError("invalid packed size K=%d N=%d planes=%d" % (K, N, planes))
     return n
@@ -280,15 +270,14 @@ def heal_packed_size(K, N, planes):
 
 def heal_maxabs_f32(x, out=None):
     """max|x| of a 2-D (or contiguous) float32 CUDA tensor, as a 1-element tensor."""
-    import torch
-    _require_dtype(x, "x", torch.float32)
-    if x.dim() == 2:
-        rows, cols, ld = x.shape[0], x.shape[1], _ld(x)
+    shape, stride = _tensor(x, "x", _f32)
+    if len(shape) == 2:
+        rows, cols, ld = shape[0], shape[1], _ld(shape, stride)
     else:
         if not x.is_contiguous():
             raise HealError("x must be 2-D or contiguous")
         rows, cols, ld = 1, x.numel(), max(x.numel(), 1)
-    out = out if out is not None else torch.empty(1, dtype=torch.float32, device=x.device)
+    out = out if out is not None else torch.empty(1, dtype=_f32, device=x.device)
     _check(lib().heal_maxabs_f32(x.data_ptr(), rows, cols, ld, out.data_ptr(), _stream()),
            "heal_maxabs_f32")
     return out
@@ -304,98 +293,85 @@ def heal_f16_weight_exponent(maxabs):
 
 def heal_pack_f16_weight(W, e, out=None):
     """Packed RNE_f16(W * 2^e) of an N x K float32 weight (torch.uint16, 1-D)."""
-    import torch
-    _require_dtype(W, "W", torch.float32, 2)
-    N, K = W.shape
+    shape, stride = _tensor(W, "W", _f32, 2)
+    N, K = shape
     size = heal_packed_size(K, N, 1)
     out = out if out is not None else torch.empty(size, dtype=torch.uint16, device=W.device)
-    _check(lib().heal_pack_f16_weight(W.data_ptr(), N, K, _ld(W), int(e), out.data_ptr(),
-                                      _stream()), "heal_pack_f16_weight")
+    _check(lib().heal_pack_f16_weight(W.data_ptr(), N, K, _ld(shape, stride), int(e),
+                                      out.data_ptr(), _stream()), "heal_pack_f16_weight")
     return out
 
 
 def heal_gemm_f16w(A, W16, N, e, products, out=None, instance=INSTANCE_AUTO):
     """HEAL-Base (products=1) or HEAL-Full (products=2): A (M x K float32) times
     the packed FP16 weight of an N x K matrix, scaled back by 2^-e."""
-    import torch
-    _require_dtype(A, "A", torch.float32, 2)
-    M, K = A.shape
-    C = out if out is not None else torch.empty((M, N), dtype=torch.float32, device=A.device)
-    _require_dtype(C, "out", torch.float32, 2)
-    if tuple(C.shape) != (M, N):
-        raise HealError("out has shape %s, expected %s" % (tuple(C.shape), (M, N)))
+    shape, stride = _tensor(A, "A", _f32, 2)
+    M, K = shape
+    C, stride_c = _output(out, A, (M, N))
     if W16.numel() < heal_packed_size(K, N, 1):
         raise HealError("W16 is smaller than the packed size")
-    _check(lib().heal_gemm_f16w_instance(int(instance), int(products), M, N, K, A.data_ptr(),
-                                         _ld(A), W16.data_ptr(), int(e), C.data_ptr(), _ld(C),
-                                         _stream()), "heal_gemm_f16w")
+    _check(_lib.heal_gemm_f16w_instance(int(instance), int(products), M, N, K, A.data_ptr(),
+                                        _ld(shape, stride), W16.data_ptr(), int(e), C.data_ptr(),
+                                        _ld((M, N), stride_c), _stream()), "heal_gemm_f16w")
     return C
 
 
 def heal_presplit_b(B, trans_b=False, out=None):
     """Packed bf16 (hi, lo) of B (K x N, or N x K with trans_b)."""
-    import torch
-    _require_dtype(B, "B", torch.float32, 2)
-    K, N = (B.shape[1], B.shape[0]) if trans_b else (B.shape[0], B.shape[1])
+    shape, stride = _tensor(B, "B", _f32, 2)
+    K, N = (shape[1], shape[0]) if trans_b else (shape[0], shape[1])
     size = heal_packed_size(K, N, 2)
     out = out if out is not None else torch.empty(size, dtype=torch.uint16, device=B.device)
-    _check(lib().heal_presplit_b(B.data_ptr(), K, N, _ld(B), 1 if trans_b else 0,
+    _check(lib().heal_presplit_b(B.data_ptr(), K, N, _ld(shape, stride), 1 if trans_b else 0,
                                  out.data_ptr(), _stream()), "heal_presplit_b")
     return out
 
 
 def heal_gemm_f32_presplit(A, Bp, N, out=None, instance=INSTANCE_AUTO):
     """C = A @ B from the pre-split packed B of an operand with N columns."""
-    import torch
-    _require_dtype(A, "A", torch.float32, 2)
-    M, K = A.shape
-    C = out if out is not None else torch.empty((M, N), dtype=torch.float32, device=A.device)
-    _require_dtype(C, "out", torch.float32, 2)
-    if tuple(C.shape) != (M, N):
-        raise HealError("out has shape %s, expected %s" % (tuple(C.shape), (M, N)))
+    shape, stride = _tensor(A, "A", _f32, 2)
+    M, K = shape
+    C, stride_c = _output(out, A, (M, N))
     if Bp.numel() < heal_packed_size(K, N, 2):
         raise HealError("Bp is smaller than the packed size")
-    _check(lib().heal_gemm_f32_presplit_instance(int(instance), M, N, K, A.data_ptr(), _ld(A),
-                                                 Bp.data_ptr(), C.data_ptr(), _ld(C), _stream()),
+    _check(_lib.heal_gemm_f32_presplit_instance(int(instance), M, N, K, A.data_ptr(),
+                                                _ld(shape, stride), Bp.data_ptr(), C.data_ptr(),
+                                                _ld((M, N), stride_c), _stream()),
            "heal_gemm_f32_presplit")
     return C
 
 
 def heal_quantize_i16(x, q=None, maxabs=None):
     """INT16 codes of a contiguous float32 CUDA tensor and its max|x| (device)."""
-    import torch
-    _require_dtype(x, "x", torch.float32)
+    _tensor(x, "x", _f32)
     if not x.is_contiguous():
         raise HealError("x must be contiguous")
     q = q if q is not None else torch.empty(x.shape, dtype=torch.int16, device=x.device)
-    maxabs = maxabs if maxabs is not None else torch.empty(1, dtype=torch.float32,
-                                                           device=x.device)
-    _check(lib().heal_quantize_i16(x.data_ptr(), x.numel(), q.data_ptr(), maxabs.data_ptr(),
-                                   _stream()), "heal_quantize_i16")
+    maxabs = maxabs if maxabs is not None else torch.empty(1, dtype=_f32, device=x.device)
+    _check((_lib or lib()).heal_quantize_i16(x.data_ptr(), x.numel(), q.data_ptr(),
+                                             maxabs.data_ptr(), _stream()), "heal_quantize_i16")
     return q, maxabs
 
 
 def heal_scores_i16(Q, Kt, maxQ, maxK, alpha=1.0, out=None):
     """Scores of INT16 codes: Q (batch x M x d), Kt (batch x N x d) -> batch x M x N
     FP32 (2-D inputs give a 2-D result)."""
-    import torch
     squeeze = Q.dim() == 2
     if squeeze:
         Q, Kt = Q.unsqueeze(0), Kt.unsqueeze(0)
         out = out.unsqueeze(0) if out is not None else None
-    _require_dtype(Q, "Q", torch.int16, 3)
-    _require_dtype(Kt, "Kt", torch.int16, 3)
-    bat, M, K = Q.shape
-    N = Kt.shape[1]
-    if Kt.shape[0] != bat or Kt.shape[2] != K:
+    shape_q, stride_q = _tensor(Q, "Q", torch.int16, 3)
+    shape_k, stride_k = _tensor(Kt, "Kt", torch.int16, 3)
+    bat, M, K = shape_q
+    N = shape_k[1]
+    if shape_k[0] != bat or shape_k[2] != K:
         raise HealError("shapes do not match: Q %s, Kt %s" % (tuple(Q.shape), tuple(Kt.shape)))
-    S = out if out is not None else torch.empty((bat, M, N), dtype=torch.float32, device=Q.device)
-    _require_dtype(S, "out", torch.float32, 3)
-    sQ = Q.stride(0) if bat > 1 else 0
-    sK = Kt.stride(0) if bat > 1 else 0
-    sS = S.stride(0) if bat > 1 else 0
-    _check(lib().heal_scores_i16(M, N, K, Q.data_ptr(), _ld(Q), sQ, maxQ.data_ptr(),
-                                 Kt.data_ptr(), _ld(Kt), sK, maxK.data_ptr(),
-                                 ctypes.c_float(alpha), S.data_ptr(), _ld(S), sS, bat,
-                                 _stream()), "heal_scores_i16")
+    S = out if out is not None else torch.empty((bat, M, N), dtype=_f32, device=Q.device)
+    shape_s, stride_s = _tensor(S, "out", _f32, 3)
+    many = bat > 1
+    _check((_lib or lib()).heal_scores_i16(
+        M, N, K, Q.data_ptr(), _ld(shape_q, stride_q), stride_q[0] if many else 0,
+        maxQ.data_ptr(), Kt.data_ptr(), _ld(shape_k, stride_k), stride_k[0] if many else 0,
+        maxK.data_ptr(), alpha, S.data_ptr(), _ld(shape_s, stride_s), stride_s[0] if many else 0,
+        bat, _stream()), "heal_scores_i16")
     return S[0] if squeeze else S

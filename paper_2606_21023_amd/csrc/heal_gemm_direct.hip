@@ -23,10 +23,14 @@
 //     while the current chunk is multiplied (PIPE), and their B is in flight
 //     RC chunks ahead.
 // Measured (4096 x 4096 weight, us, tiled kernels -> this one): 256 rows
-// HEAL-Full 72.8 -> 25.6, HEAL-Base 43.4 -> 19.4, pre-split 92.1 -> 31.8, bf16x3
-// 84.2 -> 40.6 (K x N) and 87.5 -> 41.9 (N x K); 1024 rows 85.6 -> 74.5, 53.7 ->
-// 50.6, 104.4 -> 92.7, 110.2 -> 107.3, 113.7 -> 111.0.  At 256 rows HEAL-Full
-// takes 15.7 us with neither A nor B loaded, 23.1 without A's staging.
+// HEAL-Full 72.8 -> 25.5, HEAL-Base 43.4 -> 19.4, pre-split 92.1 -> 31.8, bf16x3
+// 84.2 -> 42.5 (K x N) and 87.6 -> 45.8 (N x K); 1024 rows 85.6 -> 74.5, 53.7 ->
+// 50.6, 104.4 -> 92.7, 102.1 -> 97.3, 106.2 -> 98.2.  What is left, at 256 rows
+// HEAL-Full (28.7 us with four loading waves on 128-deep stages): 23.1 without
+// A's staging, 22.4 without loads of B, 23.0 with a quarter of the MFMAs, 15.7
+// with neither A nor B loaded: one computing wave per SIMD issues MFMAs at 0.6 of
+// their rate, and the loads, the conversion and the LDS traffic overlap it in
+// part.
 //
 // Alignment: the hardware's 16-byte buffer accesses need dword alignment only,
 // so every 4-byte aligned row takes this path.  A quad across the end of a
@@ -148,8 +152,9 @@ struct LdsA {
 // MB, NB: 16-row and 16-column blocks per wave; WVM, WVN: waves along M and N;
 // KS: 32-deep chunks per stage; RC: chunks of B in flight per wave; LW: waves
 // that stage A; RA: their register sets; PIPE: fragments of A read a chunk
-// ahead (twice the registers); TAIL: K is not a multiple of the stage depth.
-template <int OP, int BS, int MB, int WVM, int NB, int WVN, int KS, int RC, int LW, int RA, bool PIPE, bool TAIL>
+// ahead (twice the registers); TURN: B turned through LDS; TAIL: K is not a
+// multiple of the stage depth.
+template <int OP, int BS, int MB, int WVM, int NB, int WVN, int KS, int RC, int LW, int RA, bool PIPE, bool TURN, bool TAIL>
 __global__ void __launch_bounds__(64 * (WVM * WVN + LW), (WVM * WVN + LW) / 4)
 gemm_direct_kernel(DirectArgs p)
 {
@@ -167,7 +172,15 @@ gemm_direct_kernel(DirectArgs p)
     static_assert(NA >= 1 && NA * NT == BM * KQ, "whole A quads per thread");
     static_assert(BS != B_COLS || NB == 1 || NB == 2 || NB == 4, "columns per lane");
     constexpr int RB = BS == B_PACKED ? O::BP : 2;  // 16-byte registers per block and chunk
-    __shared__ __attribute__((aligned(16))) char smem[D * STAGE];
+    // TURN (B stored N x K): each wave reads whole 128-byte lines of its rows (a
+    // fragment's own order touches 16 rows, so 16 lines, with every 16 lanes) and
+    // turns them into fragments through an LDS area of its own (200 x 6144 x 4096
+    // on 64 x 128 tiles 71 -> 62 us, with eight computing waves instead of four 59;
+    // 32 x 32 tiles, which turn little at a time, are slower with it: 64 x 4096 x
+    // 4096 24.4 -> 28.1).
+    static_assert(!TURN || BS == B_ROWS, "rows of B");
+    constexpr int TURN_BYTES = TURN ? NB * 2048 : 0;
+    __shared__ __attribute__((aligned(16))) char smem[D * STAGE + CW * TURN_BYTES];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -239,7 +252,9 @@ gemm_direct_kernel(DirectArgs p)
                              ? kOOB : va[u] + (ns - 1) * BK * 4 - (k + 4 > K ? 4u * back_k : 0u);
             }
         }
-        uint32_t vb[NB];
+        constexpr int NVB = TURN ? 2 * NB : NB;
+        uint32_t vb[NVB];
+        // TURN: 16-byte unit lane % 8 of row lane / 8 of every 8 rows.
         // B_COLS: a lane's NB columns are NB*fr .. +NB-1 of the wave's; the lane
         // whose columns cross the edge of B reads them back_n early
         int back_n = 0;
@@ -248,6 +263,12 @@ gemm_direct_kernel(DirectArgs p)
             const int c = (wn * 16 + fr) * NB;
             back_n = c < cols && c + NB > cols ? c + NB - cols : 0;
             vb[0] = c < cols ? (uint32_t)((8 * fg * p.ldb + n0 + c - back_n) * 4) : kOOB;
+        } else if constexpr (TURN) {
+#pragma unroll
+            for (int u = 0; u < NVB; ++u) {
+                const int r = wn * 16 * NB + 8 * u + (lane >> 3);
+                vb[u] = r < cols ? (uint32_t)((r * p.ldb + 4 * (lane & 7)) * 4) : kOOB;
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
@@ -259,7 +280,6 @@ gemm_direct_kernel(DirectArgs p)
                                 ? (uint32_t)(((16 * jb + fr) * p.ldb + 8 * fg) * 4) : kOOB;
             }
         }
-
         // Stage s of A, or chunk kc of B, into a register set.  Those
         // past the last read nothing: every lane's offset lies beyond the buffer.
         // The scalar offset stays inside the buffer (the last stage stands in
@@ -289,6 +309,19 @@ gemm_direct_kernel(DirectArgs p)
                     const uint32_t w = TAIL ? o + so : o;
                     bload_v<NB>(r, w, TAIL ? 0 : so, v + t * NB);
                 }
+            } else if constexpr (TURN) {
+#pragma unroll
+                for (int u = 0; u < NVB; ++u) {
+                    const int so = kc * 128;
+                    const uint32_t o = vb[u] | past;
+                    uint32_t w = o;
+                    if (TAIL) {
+                        const int k = kc * 32 + 4 * (lane & 7);
+                        w = k >= K ? kOOB : o + so - (k + 4 > K ? 4u * back_k : 0u);
+                        w = (o & kOOB) ? kOOB : w;
+                    }
+                    rb[u / 2][u % 2] = bload4(r, w, TAIL ? 0 : so);
+                }
             } else {
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
@@ -306,6 +339,23 @@ gemm_direct_kernel(DirectArgs p)
                     }
                 }
             }
+        };
+        // TURN: the lines of chunk kc through this wave's LDS area into
+        // fragment order (a wave's LDS accesses are served in order: no barrier)
+        char *const area = smem + D * STAGE + wave * TURN_BYTES;
+        auto turn_b = [&](const u32x4 (*line)[RB], int kc, u32x4 (*raw)[2]) {
+            auto off = [](int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); };
+#pragma unroll
+            for (int u = 0; u < NVB; ++u) {
+                u32x4 q = line[u / 2][u % 2];
+                if (TAIL && kc == KC - 1 && kc * 32 + 4 * (lane & 7) + 4 > K) q = shift_quad(q, back_k);
+                *reinterpret_cast<u32x4 *>(area + off(8 * u + (lane >> 3), lane & 7)) = q;
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    raw[j][q] = *reinterpret_cast<const u32x4 *>(area + off(16 * j + fr, 2 * fg + q));
         };
         auto store_a = [&](char *st, const u32x4 *ra, int s) {
 #pragma unroll
@@ -339,6 +389,7 @@ gemm_direct_kernel(DirectArgs p)
             for (int i = 0; i < MB; ++i) acc[j][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
         // the two parts of B of chunk kc
+        // (TURN: rb already in fragment order, its K tail shifted)
         auto frag_b = [&](const u32x4 (*rb)[RB], int kc, u32x4 *bh, u32x4 *bl) {
             if constexpr (BS == B_PACKED) {
 #pragma unroll
@@ -356,7 +407,7 @@ gemm_direct_kernel(DirectArgs p)
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
                         u32x4 r = rb[j][q];
-                        if (TAIL && kc == KC - 1 && kc * 32 + 8 * fg + 4 * q + 4 > K)
+                        if (TAIL && !TURN && kc == KC - 1 && kc * 32 + 8 * fg + 4 * q + 4 > K)
                             r = shift_quad(r, back_k);
                         const f32x4 x = __builtin_bit_cast(f32x4, r);
                         uint32_t h0, l0, h1, l1;
@@ -441,7 +492,16 @@ gemm_direct_kernel(DirectArgs p)
             }
             __syncthreads();
             if (PIPE) frag_a(smem, 0, ah[0], al[0]);
-            if constexpr (BS != B_PACKED) {
+            u32x4 raw[TURN ? NB : 1][2];             // the next chunk's B, turned
+            if constexpr (TURN) {
+                static_assert(RC >= 2, "two chunks turned ahead");
+                turn_b(rb[0], 0, raw);
+                frag_b(raw, 0, bh[0], bl[0]);
+                turn_b(rb[1 % RC], 1, raw);
+                __builtin_amdgcn_sched_barrier(0);
+                load_b(rb[0], RC);
+                load_b(rb[1 % RC], RC + 1);
+            } else if constexpr (BS != B_PACKED) {
                 frag_b(rb[0], 0, bh[0], bl[0]);
                 __builtin_amdgcn_sched_barrier(0);
                 load_b(rb[0], RC);
@@ -465,10 +525,16 @@ gemm_direct_kernel(DirectArgs p)
                         frag_a(ks + 1 < KS ? cur : nxt, (ks + 1) % KS, ah[g % FP], al[g % FP]);
                     else
                         frag_a(cur, ks, ah[0], al[0]);
-                    if constexpr (BS != B_PACKED) frag_b(rb[n], s * KS + ks + 1, bh[g], bl[g]);
+                    const int n2 = (c + 2) % TC % RC;
+                    if constexpr (TURN) {
+                        frag_b(raw, 0, bh[g], bl[g]);
+                        turn_b(rb[n2], s * KS + ks + 2, raw);
+                    } else if constexpr (BS != B_PACKED) {
+                        frag_b(rb[n], s * KS + ks + 1, bh[g], bl[g]);
+                    }
                     mul(f, m);
                     constexpr int NM = MB * NB * (OP == OP_BASE ? 1 : OP == OP_FULL ? 2 : 3);
-                    constexpr int ND = MB * O::AP;
+                    constexpr int ND = MB * O::AP + (TURN ? 2 * NB : 0);
                     constexpr int NV = BS == B_PACKED ? (OP == OP_FULL ? 4 * NB : 0) : 26 * NB;
                     constexpr int PV = (NV + NM - 1) / NM;
                     constexpr int PD = (ND + NM - 1) / NM;
@@ -482,6 +548,7 @@ gemm_direct_kernel(DirectArgs p)
                     __builtin_amdgcn_sched_barrier(0);
                     if (reload) {
                         if constexpr (BS == B_PACKED) load_b(rb[m], s * KS + ks + RC);
+                        else if constexpr (TURN) load_b(rb[n2], s * KS + ks + 2 + RC);
                         else load_b(rb[n], s * KS + ks + 1 + RC);
                     }
                     __builtin_amdgcn_sched_barrier(0);
@@ -587,7 +654,8 @@ gemm_direct_kernel(DirectArgs p)
     }
 }
 
-template <int OP, int BS, int MB, int WVM, int NB, int WVN, int KS, int RC, int LW, int RA, bool PIPE>
+template <int OP, int BS, int MB, int WVM, int NB, int WVN, int KS, int RC, int LW, int RA, bool PIPE,
+          bool TURN = false>
 hipError_t launch_cfg(const DirectArgs &a, hipStream_t stream)
 {
     constexpr int BM = 16 * MB * WVM, BN = 16 * NB * WVN;
@@ -595,10 +663,10 @@ hipError_t launch_cfg(const DirectArgs &a, hipStream_t stream)
     const dim3 grid((unsigned)tiles, (unsigned)(a.batch < 65535 ? a.batch : 65535));
     const dim3 block(64 * (WVM * WVN + LW));
     if (a.K % (32 * KS))
-        hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, true>),
+        hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, TURN, true>),
                            grid, block, 0, stream, a);
     else
-        hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, false>),
+        hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, TURN, false>),
                            grid, block, 0, stream, a);
     return hipGetLastError();
 }
@@ -611,13 +679,14 @@ constexpr int kTileN[T_COUNT] = {32, 64, 128, 64, 128, 128, 128, 256};
 template <int OP, int BS>
 hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
 {
-    constexpr bool PACKED = BS == B_PACKED;
+    constexpr bool PACKED = BS == B_PACKED, ROWS = BS == B_ROWS;
     switch (cfg) {
-    //                                      MB WVM NB WVN KS RC LW RA PIPE
+    //                                      MB WVM NB WVN KS RC LW RA PIPE [TURN]
     case T32x32: return launch_cfg<OP, BS, 2, 1, 1, 2, 2, 4, 2, 2, true>(a, stream);
-    case T32x64: return launch_cfg<OP, BS, 2, 1, 1, 4, 2, 4, 4, 2, true>(a, stream);
+    case T32x64: return launch_cfg<OP, BS, 2, 1, 1, 4, 2, 4, 4, 2, true, ROWS>(a, stream);
     case T64x128:
         if constexpr (PACKED) return launch_cfg<OP, BS, 4, 1, 2, 4, 2, 4, 4, 4, true>(a, stream);
+        else if constexpr (ROWS) return launch_cfg<OP, BS, 4, 1, 1, 8, 2, 4, 4, 2, false, true>(a, stream);
         else return launch_cfg<OP, BS, 4, 1, 2, 4, 2, 2, 4, 2, true>(a, stream);
     case T128x128: return launch_cfg<OP, BS, 8, 1, 2, 4, 2, 2, 4, 2, false>(a, stream);
     case T96x128:
@@ -627,7 +696,7 @@ hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
         if constexpr (PACKED) return launch_cfg<OP, BS, 2, 1, 2, 4, 2, 4, 4, 4, true>(a, stream);
         break;
     case T64x64:
-        if constexpr (!PACKED) return launch_cfg<OP, BS, 4, 1, 1, 4, 4, 4, 4, 2, true>(a, stream);
+        if constexpr (!PACKED) return launch_cfg<OP, BS, 4, 1, 1, 4, 4, 4, 4, 2, true, ROWS>(a, stream);
         break;
     case T128x256:
         if constexpr (OP == OP_FULL) return launch_cfg<OP, BS, 4, 2, 4, 4, 2, 2, 4, 2, false>(a, stream);
@@ -661,13 +730,13 @@ constexpr Cost kCost[5][T_COUNT + 2] = {
      {37.6f, 49.5f, 0, 3}, {53.2f, 74, 0, 4}, {64.7f, 92.7f, 0, 5}, {0, 0, 0, 0},
      {91.5f, 104.4f, 0, 2}, {185, 273, 0, 13}},
     /* bf16x3, B stored K x N (N x K below) */
-    {{24, 28, 14, 0.8f}, {27, 31.7f, 23, 1.3f}, {0, 0, 0, 0}, {36, 40.6f, 40, 3.5f},
-     {61.3f, 66.3f, 0, 4}, {66, 83.7f, 0, 4}, {76.9f, 107.3f, 0, 6.2f}, {0, 0, 0, 0},
+    {{24, 28.5f, 12.5f, 0.8f}, {27, 31, 22, 1.3f}, {0, 0, 0, 0}, {36, 40.5f, 0, 3.5f},
+     {56, 63, 0, 4}, {65, 83.7f, 0, 4}, {76.9f, 106, 0, 6.2f}, {0, 0, 0, 0},
      {83.5f, 110, 0, 5.5f}, {200, 283, 0, 15}},
 };
 constexpr Cost kCostRows[T_COUNT + 2] = {
-    {28, 32, 18, 0.8f}, {30, 35, 32, 1.3f}, {0, 0, 0, 0}, {39, 41.9f, 41, 3.5f},
-    {68, 70.5f, 0, 4}, {72, 87.8f, 0, 4}, {81, 111, 0, 5.5f}, {0, 0, 0, 0},
+    {22, 24.4f, 17, 0.8f}, {29, 31.3f, 27, 1.3f}, {0, 0, 0, 0}, {37, 41.6f, 0, 3.5f},
+    {51, 65, 0, 4}, {72, 87.8f, 0, 4}, {81, 109, 0, 6.2f}, {0, 0, 0, 0},
     {87, 113.7f, 0, 5.5f}, {200, 283, 0, 15}};
 
 float estimate(const Cost &c, int64_t tiles, int64_t K, int cus)
@@ -686,7 +755,8 @@ float estimate(const Cost &c, int64_t tiles, int64_t K, int cus)
 // 14336 56.2 -> 35.7, 65536 145 -> 112, 128256 208 -> 225; HEAL-Base 8192 25.9 ->
 // 17.8, 16032 38.6 -> 36.4, 32064 53.2 -> 54.6, 65536 131 -> 103, 128256 201 -> 214;
 // pre-split 8192 49.0 -> 34.7, 14336 64.8 -> 57.6, 16032 58.2 -> 59.8, 65536 215 ->
-// 197; K x N 4096 23.3 -> 28.6, 8192 41.9 -> 40.2, 16032 66.8 -> 57.7, 32064 113 -> 94;
+// 197; K x N 4096 23.3 -> 28.6, 8192 41.9 -> 40.2, 10240 68.4 -> 75.3, 14336 75.9 ->
+// 61.1, 16032 66.8 -> 57.7, 32064 113 -> 94;
 // N x K 8192 40.3 -> 43.5, 14336 72.0 -> 58.2, 32064 109 -> 117.  32 rows: HEAL-Full
 // 4096 16.8 -> 19.1, 8192 24.1 -> 19.6, 16032 39.2 -> 34.6, 32064 55.0 -> 50.7;
 // pre-split 8192 28.1 -> 29.4, 16032 54.2 -> 48.8.
@@ -695,7 +765,7 @@ bool beats_skinny(int op, bool rows, const DirectArgs &a)
     if (a.batch != 1 || a.K < 256 || a.M <= 16) return false;
     const int64_t N = a.N;
     if (op == OP_BF16X3)
-        return a.M > 32 && (rows ? N >= 10240 && N <= 16384 : N >= 8192 && N <= 32768);
+        return a.M > 32 && N >= 12288 && N <= (rows ? 16384 : 32768);
     if (a.M <= 32) return N >= (op == OP_PRESPLIT ? 16000 : 8192) && N <= 32768;
     if (N >= 15360 && N < 61440 && op != OP_FULL) return false;
     return N <= 98304;

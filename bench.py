@@ -82,6 +82,7 @@ KERNEL_SOURCES = {1: ["heal_gemm_large.hip", "heal_device.h", "heal_internal.h"]
                   3: ["heal_gemm_skinny.hip", "heal_device.h", "heal_internal.h"],
                   "op": ["heal_gemm_op.hip", "heal_device.h", "heal_internal.h"],
                   "panel": ["heal_gemm_panel.hip", "heal_device.h", "heal_internal.h"],
+                  "direct": ["heal_gemm_direct.hip", "heal_device.h", "heal_internal.h"],
                   "split": ["heal_split.hip", "heal_device.h", "heal_internal.h"]}
 OP_INSTANCE_NAMES = {1: "large 128x256, 8 waves", 2: "medium 128x128, 8 waves, two register sets",
                      3: "skinny M<=64, 256-column tiles"}
@@ -169,6 +170,17 @@ def panel_applies(method, M, N, K, trans_b):
         return False
     es = 4 if method == "bf16x3" else 2
     return 0 < K <= 128 and (K * es) % 16 == 0 and N % 4 == 0 and M >= PANEL_BM[method]
+
+
+def direct_tile(method, M, N, K, trans_b, batch):
+    """(rows, columns) of the direct-B tile a product takes, or None where another
+    kernel runs it; bench.py's operands are dense and 16-byte aligned."""
+    import paper_2606_21023_amd as heal
+    kind = {"f16_base": 0, "f16_full": 1, "presplit": 3, "bf16x3": 4}.get(method)
+    if kind is None or panel_applies(method, M, N, K, trans_b):
+        return None
+    t = heal.lib().heal_gemm_direct_tile(kind, 1 if trans_b else 0, M, N, K, batch)
+    return divmod(t, 1000) if t else None
 
 
 def kernel_source_hash(instance):
@@ -608,6 +620,9 @@ def profile_summary(d, out=None):
         if cfg["method"] != "split" and panel_applies(cfg["method"], cfg["M"], cfg["N"], cfg["K"],
                                                       cfg.get("trans_b", False)):
             inst = "panel"
+        elif direct_tile(cfg["method"], cfg["M"], cfg["N"], cfg["K"], cfg.get("trans_b", False),
+                         cfg.get("batch", 1)):
+            inst = "direct"
         elif inst is None:
             import paper_2606_21023_amd as heal
             inst = heal.select_instance(cfg["M"], cfg["N"])
@@ -823,6 +838,11 @@ def main():
         traffic = measured_traffic(key, "panel")
         kernel = ("gemm_panel_kernel<%s> (%d-row A panels in LDS, 4 waves of 32 columns, "
                   "B fragments straight to registers)" % (method, PANEL_BM[method]))
+    elif direct_tile(method, w.M, w.N, w.K, w.trans_b, w.batch):
+        key = w.name if method == "bf16x3" else "%s:%s" % (method, w.name)
+        traffic = measured_traffic(key, "direct")
+        kernel = ("gemm_direct_kernel<%s> (%dx%d tiles, B straight to registers, waves that stage A)"
+                  % ((method,) + direct_tile(method, w.M, w.N, w.K, w.trans_b, w.batch)))
     elif method == "bf16x3":
         traffic = measured_traffic(w.name, instance)
         kernel = KERNEL_NAMES.get(instance, "?")

@@ -163,6 +163,13 @@ heal_status_t heal_gemm_f32_instance(int instance, int64_t M, int64_t N, int64_t
  * neither the panel nor the direct-B kernel takes the product (no HIP call). */
 int heal_gemm_select_instance(int64_t M, int64_t N);
 
+/* The tile of the direct-B kernel, as 1000 * rows + columns, that a product of
+ * dense, 16-byte aligned operands takes by itself, or 0 where another kernel
+ * runs it: kind 0 HEAL-Base, 1 HEAL-Full, 3 pre-split, 4 bf16x3 (trans_b as in
+ * heal_gemm_f32_strided_batched; the panel kernel is not considered).  For the
+ * labels of measurements. */
+int heal_gemm_direct_tile(int kind, int trans_b, int64_t M, int64_t N, int64_t K, int64_t batch);
+
 /* ==========================================================================
  * FP16 forms of the method (HEAL-Base and HEAL-Full), the pre-split B
  * operand, and the INT16 Q/K score product (HEAL+).

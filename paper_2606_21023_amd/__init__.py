@@ -84,6 +84,8 @@ def lib():
     L.heal_gemm_select_instance.argtypes = [_i64, _i64]
     L.heal_gemm_select_instance.restype = ctypes.c_int
     _c = ctypes.c_int
+    L.heal_gemm_direct_tile.argtypes = [_c, _c, _i64, _i64, _i64, _i64]
+    L.heal_gemm_direct_tile.restype = _c
     L.heal_split_f16.argtypes = [_vp, _vp, _vp, _i64, _vp]
     L.heal_split_f16.restype = _c
     L.heal_packed_size.argtypes = [_i64, _i64, _c]

@@ -247,6 +247,22 @@ heal_status_t heal_gemm_f32_instance(int instance, int64_t M, int64_t N, int64_t
 
 int heal_gemm_select_instance(int64_t M, int64_t N) { return heal::select_instance(M, N); }
 
+int heal_gemm_direct_tile(int kind, int trans_b, int64_t M, int64_t N, int64_t K, int64_t batch)
+{
+    if (kind < 0 || kind > heal::OP_BF16X3 || kind == heal::OP_SCORES || M <= 0 || N <= 0 || K <= 0 ||
+        batch <= 0)
+        return 0;
+    heal::DirectArgs a = {};
+    a.M = M;
+    a.N = N;
+    a.K = K;
+    a.lda = K;
+    a.ldb = trans_b ? K : N;
+    a.batch = batch;
+    a.vec = K % 4 == 0 && (kind != heal::OP_BF16X3 || trans_b || N % 4 == 0);
+    return heal::direct_tile(heal::direct_plan(kind, trans_b != 0, a));
+}
+
 // ---- FP16 forms, pre-split operand, INT16 scores ----------------------------
 
 heal_status_t heal_split_f16(const float *x, uint16_t *hi, uint16_t *lo, int64_t n,

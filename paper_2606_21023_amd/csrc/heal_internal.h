@@ -109,6 +109,7 @@ struct DirectArgs {
 // only).
 constexpr int DIRECT_NONE = -1, DIRECT_MEDIUM = -2;
 int direct_plan(int op, bool trans_b, const DirectArgs &args);
+int direct_tile(int plan);   // 1000 * rows + columns of a plan's tile, else 0
 hipError_t launch_direct(int op, bool trans_b, int cfg, const DirectArgs &args, hipStream_t stream);
 
 // Compute units of the current device, queried once per device.

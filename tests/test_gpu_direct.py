@@ -93,6 +93,16 @@ def test_batched(trans_b):
     _same(C, ref, "batched")
 
 
+def test_more_batch_entries_than_the_grid_has():
+    """65537 entries: some workgroups take two, one after the other."""
+    A, B = _rand((65537, 3, 5), 12), _rand((65537, 5, 5), 13)
+    announce("direct batch 65537")
+    C = heal.heal_gemm_f32_strided_batched(A, B)
+    ref = heal.heal_gemm_f32_instance(heal.INSTANCE_SKINNY, A, B)
+    torch.cuda.synchronize()
+    _same(C, ref, "batch 65537")
+
+
 def test_non_finite_rows_stay_apart():
     """Rows, columns and K positions past the edges hold zeros, so a NaN or an
     infinity in one row or column reaches its own results only."""

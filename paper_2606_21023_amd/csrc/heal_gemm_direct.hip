@@ -24,8 +24,8 @@
 //     RC chunks ahead.
 // Measured (4096 x 4096 weight, us, tiled kernels -> this one): 256 rows
 // HEAL-Full 72.8 -> 25.5, HEAL-Base 43.4 -> 19.4, pre-split 92.1 -> 31.8, bf16x3
-// 84.2 -> 42.5 (K x N) and 87.6 -> 45.8 (N x K); 1024 rows 85.6 -> 74.5, 53.7 ->
-// 50.6, 104.4 -> 92.7, 102.1 -> 97.3, 106.2 -> 98.2.  What is left, at 256 rows
+// 84.2 -> 42.5 (K x N) and 87.6 -> 45.8 (N x K); 1024 rows 85.6 -> 63.0, 53.7 ->
+// 43.4, 104.4 -> 92.7, 102.1 -> 97.3, 106.2 -> 98.2.  What is left, at 256 rows
 // HEAL-Full (28.7 us with four loading waves on 128-deep stages): 23.1 without
 // A's staging, 22.4 without loads of B, 23.0 with a quarter of the MFMAs, 15.7
 // with neither A nor B loaded: one computing wave per SIMD issues MFMAs at 0.6 of
@@ -672,9 +672,27 @@ hipError_t launch_cfg(const DirectArgs &a, hipStream_t stream)
 }
 
 // Tile configurations (rows x columns of the tile).
-enum Cfg : int { T32x32, T32x64, T32x128, T64x64, T64x128, T96x128, T128x128, T128x256, T_COUNT };
-constexpr int kTileM[T_COUNT] = {32, 32, 32, 64, 64, 96, 128, 128};
-constexpr int kTileN[T_COUNT] = {32, 64, 128, 64, 128, 128, 128, 256};
+enum Cfg : int {
+    T32x32, T32x64, T32x128, T64x64, T64x128, T64x192, T64x256, T96x128, T96x256, T128x128, T128x256,
+    T_COUNT
+};
+constexpr int kTileM[T_COUNT] = {32, 32, 32, 64, 64, 64, 64, 96, 96, 128, 128};
+constexpr int kTileN[T_COUNT] = {32, 64, 128, 64, 128, 192, 256, 128, 256, 128, 256};
+
+// The tiles of 192 and 256 columns are for packed B only: a wave that owns 48 or
+// 64 columns reads each fragment of A from LDS for three or four blocks instead
+// of two, and a column strip of 256 halves how often A is staged.  At 4096 deep,
+// one tile per CU, us, best tiles of at most 128 columns (128 x 256 HEAL-Full:
+// eight computing waves of 64 x 64) -> these:
+//              512 x 6144    1024 x 4096   1536 x 4096    2048 x 4096
+//   HEAL-Base  44.5 -> 35.5  45.7 -> 41.6  70.5 -> 53.1   87.3 -> 66.9
+//   HEAL-Full  65.3 -> 49.8  70.6 -> 61.5  111 -> 85.5    121 -> 111
+//   pre-split  72.7 -> 65.0  (83.0, 85.1)  134 -> 117     165 -> 153
+// The pre-split product has no 64 x 256 tile (85.1 above, 83.0 on 128 x 128).  The
+// 128-column tiles stay for outputs whose width they divide better (HEAL-Base
+// 7059 x 1141 x 8301 128 x 128 237, 64 x 128 271 us).
+// With an FP32 B, whose raw quads and both parts are held too, they spill
+// (1024 x 4096 K x N: 64 x 256 tiles 179 us, 98 on the tiles it takes now).
 
 template <int OP, int BS>
 hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
@@ -688,6 +706,15 @@ hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
         if constexpr (PACKED) return launch_cfg<OP, BS, 4, 1, 2, 4, 2, 4, 4, 4, true>(a, stream);
         else if constexpr (ROWS) return launch_cfg<OP, BS, 4, 1, 1, 8, 2, 4, 4, 2, false, true>(a, stream);
         else return launch_cfg<OP, BS, 4, 1, 2, 4, 2, 2, 4, 2, true>(a, stream);
+    case T64x192:
+        if constexpr (PACKED) return launch_cfg<OP, BS, 4, 1, 3, 4, 2, 2, 4, 2, true>(a, stream);
+        break;
+    case T64x256:
+        if constexpr (OP == OP_BASE || OP == OP_FULL) return launch_cfg<OP, BS, 4, 1, 4, 4, 2, 2, 4, 2, true>(a, stream);
+        break;
+    case T96x256:
+        if constexpr (PACKED) return launch_cfg<OP, BS, 6, 1, 4, 4, 1, 2, 4, 4, false>(a, stream);
+        break;
     case T128x128: return launch_cfg<OP, BS, 8, 1, 2, 4, 2, 2, 4, 2, false>(a, stream);
     case T96x128:
         if constexpr (PACKED) return launch_cfg<OP, BS, 6, 1, 2, 4, 2, 4, 4, 4, false>(a, stream);
@@ -699,7 +726,7 @@ hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
         if constexpr (!PACKED) return launch_cfg<OP, BS, 4, 1, 1, 4, 4, 4, 4, 2, true, ROWS>(a, stream);
         break;
     case T128x256:
-        if constexpr (OP == OP_FULL) return launch_cfg<OP, BS, 4, 2, 4, 4, 2, 2, 4, 2, false>(a, stream);
+        if constexpr (PACKED) return launch_cfg<OP, BS, 8, 1, 4, 4, 1, 2, 4, 2, false>(a, stream);
         break;
     }
     return hipErrorInvalidValue;
@@ -714,29 +741,34 @@ hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
 constexpr int kMedium = T_COUNT, kLarge = T_COUNT + 1;
 struct Cost { float few, full, more, fixed; };
 constexpr Cost kCost[5][T_COUNT + 2] = {
-    // 32x32, 32x64, 32x128, 64x64; 64x128, 96x128, 128x128, 128x256; medium, large
+    // 32x32, 32x64, 32x128, 64x64; 64x128, 64x192, 64x256; 96x128, 96x256; 128x128, 128x256; medium, large
     /* HEAL-Base */
     {{13, 15, 7.5f, 0.8f}, {14, 17.6f, 11, 1.1f}, {17.5f, 19.4f, 16, 1.6f}, {0, 0, 0, 0},
-     {23.1f, 28, 0, 3}, {29, 38.4f, 0, 5}, {39.5f, 50.6f, 0, 5}, {0, 0, 0, 0},
+     {23.1f, 28, 0, 3}, {33.5f, 40, 0, 3.8f}, {35, 46, 0, 4},
+     {29, 38.4f, 0, 5}, {42.9f, 57, 0, 7.5f}, {39.5f, 50.6f, 0, 5}, {51, 70, 0, 12},
      {42, 53.7f, 0, 2}, {82, 122, 0, 13}},
     /* HEAL-Full */
     {{15, 18.5f, 8.8f, 0.8f}, {16, 21, 13.3f, 1.1f}, {19.8f, 25.6f, 21, 1.6f}, {0, 0, 0, 0},
-     {29.9f, 40.4f, 0, 3}, {43.3f, 57.5f, 0, 5}, {57, 74.5f, 0, 5}, {93, 134, 0, 11},
-     {72.5f, 85.6f, 0, 2.3f}, {150, 216, 0, 13}},
+     {29.9f, 40.4f, 0, 3}, {39, 52, 0, 6}, {49.7f, 66, 0, 5},
+     {43.3f, 57.5f, 0, 5}, {70.5f, 92.5f, 0, 5.5f}, {57, 74.5f, 0, 5}, {91.3f, 118.5f, 0, 10},
+     {72.5f, 85.6f, 0, 2.3f}, {150, 216, 0, 12}},
     /* (INT16 scores: not here) */
     {},
     /* pre-split */
     {{17, 20, 11.5f, 0.8f}, {18, 22.2f, 17.5f, 1.1f}, {27.3f, 31.8f, 30, 1.8f}, {0, 0, 0, 0},
-     {37.6f, 49.5f, 0, 3}, {53.2f, 74, 0, 5}, {64.7f, 92.7f, 0, 5}, {0, 0, 0, 0},
+     {37.6f, 49.5f, 0, 3}, {59, 74, 0, 5.5f}, {0, 0, 0, 0},
+     {53.2f, 74, 0, 5}, {106.9f, 127, 0, 7}, {64.7f, 92.7f, 0, 5}, {137, 162.5f, 0, 12.5f},
      {91.5f, 104.4f, 0, 2.7f}, {185, 273, 0, 13}},
     /* bf16x3, B stored K x N (N x K below) */
     {{24, 28.5f, 12.5f, 0.8f}, {27, 31, 22, 1.3f}, {0, 0, 0, 0}, {36, 40.5f, 0, 3.5f},
-     {56, 63, 0, 4}, {65, 83.7f, 0, 4.8f}, {76.9f, 106, 0, 6.2f}, {0, 0, 0, 0},
+     {56, 63, 0, 4}, {0, 0, 0, 0}, {0, 0, 0, 0},
+     {65, 83.7f, 0, 4.8f}, {0, 0, 0, 0}, {76.9f, 106, 0, 6.2f}, {0, 0, 0, 0},
      {83.5f, 110, 0, 5.5f}, {200, 283, 0, 15}},
 };
 constexpr Cost kCostRows[T_COUNT + 2] = {
     {22, 24.4f, 17, 0.8f}, {29, 31.3f, 27, 1.3f}, {0, 0, 0, 0}, {37, 41.6f, 0, 3.5f},
-    {51, 65, 0, 4}, {72, 87.8f, 0, 4.8f}, {81, 109, 0, 6.2f}, {0, 0, 0, 0},
+    {51, 65, 0, 4}, {0, 0, 0, 0}, {0, 0, 0, 0},
+    {72, 87.8f, 0, 4.8f}, {0, 0, 0, 0}, {81, 109, 0, 6.2f}, {0, 0, 0, 0},
     {87, 113.7f, 0, 5.5f}, {200, 283, 0, 15}};
 
 float estimate(const Cost &c, int64_t tiles, int64_t K, int cus)

@@ -26,8 +26,6 @@ Functions (names follow the C ABI):
 import ctypes
 import os
 
-import torch
-
 __all__ = ["HealError", "lib", "library_path", "build_id", "check_build", "heal_split_f32", "heal_gemm_f32",
            "heal_gemm_f32_strided_batched", "heal_gemm_f32_instance", "select_instance",
            "INSTANCE_AUTO", "INSTANCE_LARGE", "INSTANCE_MEDIUM", "INSTANCE_SKINNY", "STATUS",
@@ -137,15 +135,31 @@ def _check(status, what):
         raise HealError("%s failed: %s" % (what, STATUS.get(status, status)), status)
 
 
+class _Torch:
+    """Stands for the module until a call needs it: the C library is built, and
+    its host functions are called, without PyTorch."""
+
+    def __getattr__(self, name):
+        import importlib
+        globals()["torch"] = module = importlib.import_module("torch")
+        return getattr(module, name)
+
+
+torch = _Torch()
+
+
 def _stream():
     """The current device's current stream, as a raw pointer.  (The Stream object
-    of torch.cuda.current_stream costs 3 us, a third of a small call.)"""
-    return _raw_stream(_current_device())
-
-
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
-_f32 = torch.float32
+    of torch.cuda.current_stream costs 3 us, a third of a small call; it stands in
+    where torch lacks the raw accessors.)  The first call replaces itself."""
+    global _stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        _stream = lambda: torch.cuda.current_stream().cuda_stream
+    else:
+        _stream = lambda: raw(device())
+    return _stream()
 
 
 def _tensor(t, name, dtype, ndim=None):
@@ -175,7 +189,7 @@ def _output(out, like, shape):
     if out is None:
         C = like.new_empty(shape)
         return C, C.stride()
-    got, stride = _tensor(out, "out", _f32, len(shape))
+    got, stride = _tensor(out, "out", torch.float32, len(shape))
     if tuple(got) != shape:
         raise HealError("out has shape %s, expected %s" % (tuple(got), shape))
     return out, stride
@@ -202,8 +216,8 @@ def _split(what, x, hi, lo):
 
 def heal_gemm_f32(A, B, out=None):
     """C = A @ B (A: M x K, B: K x N, row-major float32 CUDA tensors)."""
-    shape_a, stride_a = _tensor(A, "A", _f32, 2)
-    shape_b, stride_b = _tensor(B, "B", _f32, 2)
+    shape_a, stride_a = _tensor(A, "A", torch.float32, 2)
+    shape_b, stride_b = _tensor(B, "B", torch.float32, 2)
     M, K = shape_a
     N = shape_b[1]
     if shape_b[0] != K:
@@ -216,8 +230,8 @@ def heal_gemm_f32(A, B, out=None):
 
 
 def _batched(fn_args_prefix, A, B, alpha, trans_b, out, what):
-    shape_a, stride_a = _tensor(A, "A", _f32, 3)
-    shape_b, stride_b = _tensor(B, "B", _f32, 3)
+    shape_a, stride_a = _tensor(A, "A", torch.float32, 3)
+    shape_b, stride_b = _tensor(B, "B", torch.float32, 3)
     bat, M, K = shape_a
     N, Kb = (shape_b[1], shape_b[2]) if trans_b else (shape_b[2], shape_b[1])
     if Kb != K or shape_b[0] != bat:
@@ -272,14 +286,14 @@ def heal_packed_size(K, N, planes):
 
 def heal_maxabs_f32(x, out=None):
     """max|x| of a 2-D (or contiguous) float32 CUDA tensor, as a 1-element tensor."""
-    shape, stride = _tensor(x, "x", _f32)
+    shape, stride = _tensor(x, "x", torch.float32)
     if len(shape) == 2:
         rows, cols, ld = shape[0], shape[1], _ld(shape, stride)
     else:
         if not x.is_contiguous():
             raise HealError("x must be 2-D or contiguous")
         rows, cols, ld = 1, x.numel(), max(x.numel(), 1)
-    out = out if out is not None else torch.empty(1, dtype=_f32, device=x.device)
+    out = out if out is not None else torch.empty(1, dtype=torch.float32, device=x.device)
     _check(lib().heal_maxabs_f32(x.data_ptr(), rows, cols, ld, out.data_ptr(), _stream()),
            "heal_maxabs_f32")
     return out
@@ -295,7 +309,7 @@ def heal_f16_weight_exponent(maxabs):
 
 def heal_pack_f16_weight(W, e, out=None):
     """Packed RNE_f16(W * 2^e) of an N x K float32 weight (torch.uint16, 1-D)."""
-    shape, stride = _tensor(W, "W", _f32, 2)
+    shape, stride = _tensor(W, "W", torch.float32, 2)
     N, K = shape
     size = heal_packed_size(K, N, 1)
     out = out if out is not None else torch.empty(size, dtype=torch.uint16, device=W.device)
@@ -307,7 +321,7 @@ def heal_pack_f16_weight(W, e, out=None):
 def heal_gemm_f16w(A, W16, N, e, products, out=None, instance=INSTANCE_AUTO):
     """HEAL-Base (products=1) or HEAL-Full (products=2): A (M x K float32) times
     the packed FP16 weight of an N x K matrix, scaled back by 2^-e."""
-    shape, stride = _tensor(A, "A", _f32, 2)
+    shape, stride = _tensor(A, "A", torch.float32, 2)
     M, K = shape
     C, stride_c = _output(out, A, (M, N))
     if W16.numel() < heal_packed_size(K, N, 1):
@@ -320,7 +334,7 @@ def heal_gemm_f16w(A, W16, N, e, products, out=None, instance=INSTANCE_AUTO):
 
 def heal_presplit_b(B, trans_b=False, out=None):
     """Packed bf16 (hi, lo) of B (K x N, or N x K with trans_b)."""
-    shape, stride = _tensor(B, "B", _f32, 2)
+    shape, stride = _tensor(B, "B", torch.float32, 2)
     K, N = (shape[1], shape[0]) if trans_b else (shape[0], shape[1])
     size = heal_packed_size(K, N, 2)
     out = out if out is not None else torch.empty(size, dtype=torch.uint16, device=B.device)
@@ -331,7 +345,7 @@ def heal_presplit_b(B, trans_b=False, out=None):
 
 def heal_gemm_f32_presplit(A, Bp, N, out=None, instance=INSTANCE_AUTO):
     """C = A @ B from the pre-split packed B of an operand with N columns."""
-    shape, stride = _tensor(A, "A", _f32, 2)
+    shape, stride = _tensor(A, "A", torch.float32, 2)
     M, K = shape
     C, stride_c = _output(out, A, (M, N))
     if Bp.numel() < heal_packed_size(K, N, 2):
@@ -345,11 +359,11 @@ def heal_gemm_f32_presplit(A, Bp, N, out=None, instance=INSTANCE_AUTO):
 
 def heal_quantize_i16(x, q=None, maxabs=None):
     """INT16 codes of a contiguous float32 CUDA tensor and its max|x| (device)."""
-    _tensor(x, "x", _f32)
+    _tensor(x, "x", torch.float32)
     if not x.is_contiguous():
         raise HealError("x must be contiguous")
     q = q if q is not None else torch.empty(x.shape, dtype=torch.int16, device=x.device)
-    maxabs = maxabs if maxabs is not None else torch.empty(1, dtype=_f32, device=x.device)
+    maxabs = maxabs if maxabs is not None else torch.empty(1, dtype=torch.float32, device=x.device)
     _check((_lib or lib()).heal_quantize_i16(x.data_ptr(), x.numel(), q.data_ptr(),
                                              maxabs.data_ptr(), _stream()), "heal_quantize_i16")
     return q, maxabs
@@ -368,8 +382,8 @@ def heal_scores_i16(Q, Kt, maxQ, maxK, alpha=1.0, out=None):
     N = shape_k[1]
     if shape_k[0] != bat or shape_k[2] != K:
         raise HealError("shapes do not match: Q %s, Kt %s" % (tuple(Q.shape), tuple(Kt.shape)))
-    S = out if out is not None else torch.empty((bat, M, N), dtype=_f32, device=Q.device)
-    shape_s, stride_s = _tensor(S, "out", _f32, 3)
+    S = out if out is not None else torch.empty((bat, M, N), dtype=torch.float32, device=Q.device)
+    shape_s, stride_s = _tensor(S, "out", torch.float32, 3)
     many = bat > 1
     _check((_lib or lib()).heal_scores_i16(
         M, N, K, Q.data_ptr(), _ld(shape_q, stride_q), stride_q[0] if many else 0,

@@ -172,7 +172,7 @@ def _tensor(t, name, dtype, ndim=None):
     shape, stride = t.shape, t.stride()
     if ndim is not None and len(shape) != ndim:
         raise HealError("%s must have %d dimensions, got %d" % (name, ndim, len(shape)))
-    if shape and stride[-1] != 1 and shape[-1] > 1 and t.numel():
+    if stride[-1] != 1 and shape[-1] > 1 and t.numel():   # (0 dimensions: IndexError)
         # (a last dimension of one element has no stride to respect: torch
         # may report any, e.g. for the transpose of a one-row matrix)
         raise HealError("%s must be contiguous in its last dimension" % name)
@@ -187,7 +187,9 @@ def _ld(shape, stride):
 def _output(out, like, shape):
     """`out`, checked, or a new float32 tensor; and its strides."""
     if out is None:
-        C = like.new_empty(shape)
+        # (new_empty is 0.6 us faster, but follows a subclass)
+        C = (like.new_empty(shape) if type(like) is torch.Tensor
+             else torch.empty(shape, dtype=torch.float32, device=like.device))
         return C, C.stride()
     got, stride = _tensor(out, "out", torch.float32, len(shape))
     if tuple(got) != shape:
@@ -239,7 +241,7 @@ def _batched(fn_args_prefix, A, B, alpha, trans_b, out, what):
                         % (tuple(A.shape), tuple(B.shape), trans_b))
     C, stride_c = _output(out, A, (bat, M, N))
     many = bat > 1
-    st = fn_args_prefix(M, N, K, alpha, A.data_ptr(), _ld(shape_a, stride_a),
+    st = fn_args_prefix(M, N, K, ctypes.c_float(alpha), A.data_ptr(), _ld(shape_a, stride_a),
                         stride_a[0] if many else 0, B.data_ptr(), _ld(shape_b, stride_b),
                         stride_b[0] if many else 0, 1 if trans_b else 0, C.data_ptr(),
                         _ld((M, N), stride_c), stride_c[0] if many else 0, bat, _stream())
@@ -388,6 +390,6 @@ def heal_scores_i16(Q, Kt, maxQ, maxK, alpha=1.0, out=None):
     _check((_lib or lib()).heal_scores_i16(
         M, N, K, Q.data_ptr(), _ld(shape_q, stride_q), stride_q[0] if many else 0,
         maxQ.data_ptr(), Kt.data_ptr(), _ld(shape_k, stride_k), stride_k[0] if many else 0,
-        maxK.data_ptr(), alpha, S.data_ptr(), _ld(shape_s, stride_s), stride_s[0] if many else 0,
+        maxK.data_ptr(), ctypes.c_float(alpha), S.data_ptr(), _ld(shape_s, stride_s), stride_s[0] if many else 0,
         bat, _stream()), "heal_scores_i16")
     return S[0] if squeeze else S

@@ -610,31 +610,45 @@ hipError_t launch_tile(const GemmArgs &a, bool trans_b, bool use_alpha, hipStrea
 
 }  // namespace
 
+static DirectArgs direct_args(const GemmArgs &a, bool trans_b)
+{
+    DirectArgs d = {};
+    d.M = a.M;
+    d.N = a.N;
+    d.K = a.K;
+    d.A = a.A;
+    d.lda = a.lda;
+    d.strideA = a.strideA;
+    d.B = a.B;
+    d.ldb = a.ldb;
+    d.strideB = a.strideB;
+    d.C = a.C;
+    d.ldc = a.ldc;
+    d.strideC = a.strideC;
+    d.batch = a.batch;
+    d.alpha = a.alpha;
+    d.vec = a.vecA && a.vecB && a.K % 4 == 0 && (trans_b || a.N % 4 == 0);
+    return d;
+}
+
+Route choose_gemm(const GemmArgs &a, bool trans_b)
+{
+    if (HEAL_PANEL && panel_kernel_applies(a, trans_b)) return {ROUTE_PANEL, 0};
+    const int plan = direct_plan(OP_BF16X3, trans_b, direct_args(a, trans_b));
+    if (plan >= 0) return {ROUTE_DIRECT, plan};
+    return {plan == DIRECT_MEDIUM ? HEAL_INSTANCE_MEDIUM
+            : plan == DIRECT_LARGE ? HEAL_INSTANCE_LARGE : select_instance(a.M, a.N), 0};
+}
+
 hipError_t launch_gemm(int instance, const GemmArgs &a, bool trans_b, bool use_alpha,
                        hipStream_t stream)
 {
     if (instance == HEAL_INSTANCE_AUTO) {
-        if (HEAL_PANEL && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
-        instance = select_instance(a.M, a.N);
-        DirectArgs d = {};
-        d.M = a.M;
-        d.N = a.N;
-        d.K = a.K;
-        d.A = a.A;
-        d.lda = a.lda;
-        d.strideA = a.strideA;
-        d.B = a.B;
-        d.ldb = a.ldb;
-        d.strideB = a.strideB;
-        d.C = a.C;
-        d.ldc = a.ldc;
-        d.strideC = a.strideC;
-        d.batch = a.batch;
-        d.alpha = a.alpha;
-        d.vec = a.vecA && a.vecB && a.K % 4 == 0 && (trans_b || a.N % 4 == 0);
-        const int plan = direct_plan(OP_BF16X3, trans_b, d);
-        if (plan >= 0) return launch_direct(OP_BF16X3, trans_b, plan, d, stream);
-        if (plan == DIRECT_MEDIUM) instance = HEAL_INSTANCE_MEDIUM;
+        const Route r = choose_gemm(a, trans_b);
+        if (r.kernel == ROUTE_PANEL) return launch_gemm_panel(a, use_alpha, stream);
+        if (r.kernel == ROUTE_DIRECT)
+            return launch_direct(OP_BF16X3, trans_b, r.plan, direct_args(a, trans_b), stream);
+        instance = r.kernel;
     }
     switch (instance) {
     case HEAL_INSTANCE_LARGE:

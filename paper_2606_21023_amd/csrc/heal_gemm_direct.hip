@@ -836,6 +836,7 @@ int direct_plan(int op, bool trans_b, const DirectArgs &a)
         if (nl > cus)
             best = 0.5f * (best + (cost[kLarge].fixed + cost[kLarge].full * (float)a.K / 4096.0f) *
                                       (float)nl / (float)cus);
+        plan = DIRECT_LARGE;
         const float t = estimate(cost[kMedium], tiles(128, 128), a.K, cus);
         if (t < best) {
             best = t;

@@ -1483,28 +1483,40 @@ int device_cus()
     return n;
 }
 
+static DirectArgs direct_args(const OpArgs &a)
+{
+    DirectArgs d = {};
+    d.M = a.M;
+    d.N = a.N;
+    d.K = a.K;
+    d.A = static_cast<const float *>(a.A);
+    d.lda = a.lda;
+    d.B = a.B;
+    d.C = a.C;
+    d.ldc = a.ldc;
+    d.batch = a.batch;
+    d.e = a.e;
+    d.vec = a.vecA && a.K % 4 == 0;
+    return d;
+}
+
+Route choose_op(int op, const OpArgs &a)
+{
+    if (op == OP_SCORES)
+        return {HEAL_PANEL && scores_panel_applies(a) ? ROUTE_PANEL : select_instance(a.M, a.N), 0};
+    const int plan = direct_plan(op, false, direct_args(a));
+    if (plan >= 0) return {ROUTE_DIRECT, plan};
+    return {plan == DIRECT_MEDIUM ? HEAL_INSTANCE_MEDIUM
+            : plan == DIRECT_LARGE ? HEAL_INSTANCE_LARGE : select_instance(a.M, a.N), 0};
+}
+
 hipError_t launch_gemm_op(int op, int instance, const OpArgs &a, hipStream_t stream)
 {
     if (instance == HEAL_INSTANCE_AUTO) {
-        if (HEAL_PANEL && op == OP_SCORES && scores_panel_applies(a)) return launch_scores_panel(a, stream);
-        instance = select_instance(a.M, a.N);
-        if (op != OP_SCORES) {
-            DirectArgs d = {};
-            d.M = a.M;
-            d.N = a.N;
-            d.K = a.K;
-            d.A = static_cast<const float *>(a.A);
-            d.lda = a.lda;
-            d.B = a.B;
-            d.C = a.C;
-            d.ldc = a.ldc;
-            d.batch = a.batch;
-            d.e = a.e;
-            d.vec = a.vecA && a.K % 4 == 0;
-            const int plan = direct_plan(op, false, d);
-            if (plan >= 0) return launch_direct(op, false, plan, d, stream);
-            if (plan == DIRECT_MEDIUM) instance = HEAL_INSTANCE_MEDIUM;
-        }
+        const Route r = choose_op(op, a);
+        if (r.kernel == ROUTE_PANEL) return launch_scores_panel(a, stream);
+        if (r.kernel == ROUTE_DIRECT) return launch_direct(op, false, r.plan, direct_args(a), stream);
+        instance = r.kernel;
     }
     switch (op) {
     case OP_BASE: return launch_op<OP_BASE>(instance, a, stream);

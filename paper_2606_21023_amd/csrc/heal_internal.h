@@ -26,7 +26,17 @@ struct GemmArgs {
 // The instance of an M x N output by size (heal_instance_t in heal.h).
 int select_instance(int64_t M, int64_t N);
 
-// instance: HEAL_INSTANCE_*; AUTO chooses, the direct-B kernel included.
+// What an automatic call runs on: an instance (HEAL_INSTANCE_*), or one of the
+// two kernels that only automatic calls reach everywhere; plan: the direct-B
+// kernel's tile configuration.
+constexpr int ROUTE_PANEL = 8, ROUTE_DIRECT = 9;
+struct Route {
+    int kernel;
+    int plan;
+};
+Route choose_gemm(const GemmArgs &args, bool trans_b);   // host only
+
+// instance: HEAL_INSTANCE_*; AUTO runs what choose_gemm says.
 hipError_t launch_gemm(int instance, const GemmArgs &args, bool trans_b, bool use_alpha,
                        hipStream_t stream);
 
@@ -104,10 +114,10 @@ struct DirectArgs {
 };
 
 // The tile configuration (>= 0) of the direct-B kernel that a product should
-// take; DIRECT_MEDIUM where the 128 x 128 staged tiles are faster; DIRECT_NONE
-// where it cannot run the call, or the large or skinny kernels are faster (host
-// only).
-constexpr int DIRECT_NONE = -1, DIRECT_MEDIUM = -2;
+// take; DIRECT_MEDIUM or DIRECT_LARGE where the 128 x 128 or the 256 x 256 staged
+// tiles are faster; DIRECT_NONE where it cannot run the call or the skinny
+// kernels are faster: the instance of the output's size then runs it (host only).
+constexpr int DIRECT_NONE = -1, DIRECT_MEDIUM = -2, DIRECT_LARGE = -3;
 int direct_plan(int op, bool trans_b, const DirectArgs &args);
 int direct_tile(int plan);   // 1000 * rows + columns of a plan's tile, else 0
 hipError_t launch_direct(int op, bool trans_b, int cfg, const DirectArgs &args, hipStream_t stream);
@@ -115,7 +125,9 @@ hipError_t launch_direct(int op, bool trans_b, int cfg, const DirectArgs &args, 
 // Compute units of the current device, queried once per device.
 int device_cus();
 
-// instance: HEAL_INSTANCE_* (AUTO chooses from M and N).
+Route choose_op(int op, const OpArgs &args);             // host only
+
+// instance: HEAL_INSTANCE_*; AUTO runs what choose_op says.
 hipError_t launch_gemm_op(int op, int instance, const OpArgs &args, hipStream_t stream);
 
 hipError_t launch_split_f16(const float *x, uint16_t *hi, uint16_t *lo, int64_t n,

@@ -168,8 +168,12 @@ __device__ __forceinline__ void split8(const u32x4 *raw, u32x4 &h, u32x4 &l)
 // by alpha.  PD: steps of B loads in flight per wave.  PBM: rows of the
 // panel (128: two workgroups per CU; 256: one, B read from L2 half as often).
 // RAG: rows of C that are not whole 128-byte lines apart, or N % 4 != 0.
+// Waves per SIMD: three for the INT16 panels of at most 64 rows, but two for 32
+// rows at full depth, which spilled 11 registers (29 with RAG) under the bound of
+// three (32 heads of 32 x 3001 x 128 18.8 -> 10.8 us, 64 of 17 x 16384 84 -> 56).
 template <bool SCORES, bool SCALE, int KC, int PD, int PBM, bool RAG>
-__global__ void __launch_bounds__(PNT, PBM <= 64 ? (SCORES ? 3 : 2) : PBM <= 128 ? 2 : 1) gemm_panel_kernel(PanelArgs p)
+__global__ void __launch_bounds__(PNT, PBM <= 64   ? (SCORES && !(PBM == 32 && KC == 4) ? 3 : 2)
+                                       : PBM <= 128 ? 2 : 1) gemm_panel_kernel(PanelArgs p)
 {
     constexpr int PRB = PBM / 16;               // 16-row blocks of the panel
     constexpr int PPLANE = PBM * PRP;           // one LDS plane of the panel

@@ -662,10 +662,14 @@ hipError_t launch_cfg(const DirectArgs &a, hipStream_t stream)
     const int64_t tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
     const dim3 grid((unsigned)tiles, (unsigned)(a.batch < 65535 ? a.batch : 65535));
     const dim3 block(64 * (WVM * WVN + LW));
-    if (a.K % (32 * KS))
-        hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, TURN, true>),
-                           grid, block, 0, stream, a);
-    else
+    if (a.K % (32 * KS)) {
+        // (direct_plan keeps K tails off the 128 x 128 tiles of an FP32 B, whose
+        // form spilled 27 and 49 registers)
+        if constexpr (BS != B_PACKED && BM == 128) return hipErrorInvalidValue;
+        else
+            hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, TURN, true>),
+                               grid, block, 0, stream, a);
+    } else
         hipLaunchKernelGGL((gemm_direct_kernel<OP, BS, MB, WVM, NB, WVN, KS, RC, LW, RA, PIPE, TURN, false>),
                            grid, block, 0, stream, a);
     return hipGetLastError();
@@ -846,7 +850,7 @@ int direct_plan(int op, bool trans_b, const DirectArgs &a)
     for (int c = 0; c < T_COUNT; ++c) {
         const int64_t n = tiles(kTileM[c], kTileN[c]);
         if (cost[c].full <= 0.0f || n > (1 << 20)) continue;
-        // (its K-tail form spills registers)
+        // (no K-tail form: launch_cfg)
         if (c == T128x128 && op == OP_BF16X3 && a.K % 64 != 0) continue;
         // the forms with a K tail take 0.5 us more (4096 x 512 x 100 HEAL-Full 8.7 us
         // on 64 x 128 tiles, 7.5 on the staged 128 x 128 ones)

@@ -32,9 +32,6 @@ KNOWN = {
     "gemm_direct_kernel<3, 0, 6, 1, 4, 4, 1, 2, 4, 4, false, false, true>": 10,
     # 64 x 64
     "gemm_direct_kernel<4, 2, 4, 1, 1, 4, 4, 4, 4, 2, true, false, true>": 4,
-    # 128 x 128, FP32 B
-    "gemm_direct_kernel<4, 1, 8, 1, 2, 4, 2, 2, 4, 2, false, false, true>": 49,
-    "gemm_direct_kernel<4, 2, 8, 1, 2, 4, 2, 2, 4, 2, false, false, true>": 27,
 }
 
 

@@ -341,16 +341,18 @@ gemm_direct_kernel(DirectArgs p)
             }
         };
         // TURN: the lines of chunk kc through this wave's LDS area into
-        // fragment order (a wave's LDS accesses are served in order: no barrier)
+        // fragment order (one wave's own area: no barrier, only their order)
         char *const area = smem + D * STAGE + wave * TURN_BYTES;
         auto turn_b = [&](const u32x4 (*line)[RB], int kc, u32x4 (*raw)[2]) {
             auto off = [](int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); };
+            wave_lds_order();
 #pragma unroll
             for (int u = 0; u < NVB; ++u) {
                 u32x4 q = line[u / 2][u % 2];
                 if (TAIL && kc == KC - 1 && kc * 32 + 4 * (lane & 7) + 4 > K) q = shift_quad(q, back_k);
                 *reinterpret_cast<u32x4 *>(area + off(8 * u + (lane >> 3), lane & 7)) = q;
             }
+            wave_lds_order();
 #pragma unroll
             for (int j = 0; j < NB; ++j)
 #pragma unroll

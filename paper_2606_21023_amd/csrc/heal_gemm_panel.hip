@@ -331,12 +331,14 @@ __global__ void __launch_bounds__(PNT, PBM <= 64   ? (SCORES && !(PBM == 32 && K
         const int s = EDGE ? (int)all_steps - 1 : step_of(clamp(t));
         u32x4 bh[2][KC], bl[2][KC];
         if constexpr (TURN) {
-            // (a wave's LDS accesses are served in order: no barrier)
+            // (one wave's own area: no barrier, only their order)
+            wave_lds_order();
 #pragma unroll
             for (int u = 0; u < NBU; ++u) {
                 const int q = u * 64 + lane, r = q / UPR, c = q % UPR;
                 *reinterpret_cast<u32x4 *>(turn + turn_off(r, c)) = line[set][u];
             }
+            wave_lds_order();
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll

@@ -250,7 +250,7 @@ int heal_gemm_select_instance(int64_t M, int64_t N) { return heal::select_instan
 int heal_gemm_direct_tile(int kind, int trans_b, int64_t M, int64_t N, int64_t K, int64_t batch)
 {
     if (kind < 0 || kind > heal::OP_BF16X3 || kind == heal::OP_SCORES || M <= 0 || N <= 0 || K <= 0 ||
-        batch <= 0)
+        batch <= 0 || !product_fits(M, N) || batch > ((int64_t)1 << 62) / (M * N))
         return 0;
     heal::DirectArgs a = {};
     a.M = M;
@@ -258,6 +258,8 @@ int heal_gemm_direct_tile(int kind, int trans_b, int64_t M, int64_t N, int64_t K
     a.K = K;
     a.lda = K;
     a.ldb = trans_b ? K : N;
+    a.ldc = N;
+    a.strideC = M * N;
     a.batch = batch;
     a.vec = K % 4 == 0 && (kind != heal::OP_BF16X3 || trans_b || N % 4 == 0);
     return heal::direct_tile(heal::direct_plan(kind, trans_b != 0, a));

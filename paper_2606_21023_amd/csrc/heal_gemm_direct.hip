@@ -738,54 +738,110 @@ hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)
     return hipErrorInvalidValue;
 }
 
-// Time of one launch by kernel: us at 4096 deep with 64 tiles, with 256 (one
-// per CU) and per further 256 tiles (0: one tile per CU at a time, so whole
-// rounds), and a fixed part per 256 tiles (the first loads and C).  Measured
-// on 128 to 3072 x 4096 x 4096 products and on products 64 to 512 deep; the last
-// two are the 128 x 128 and the 256 x 256 tiles of the staged kernels.  The
-// smallest of these estimates picks the tile; 0: not built.
-constexpr int kMedium = T_COUNT, kLarge = T_COUNT + 1;
-struct Cost { float few, full, more, fixed; };
-constexpr Cost kCost[5][T_COUNT + 2] = {
-    // 32x32, 32x64, 32x128, 64x64; 64x128, 64x192, 64x256; 96x128, 96x256; 128x128, 128x256; medium, large
-    /* HEAL-Base */
-    {{13, 15, 7.5f, 0.8f}, {14, 17.6f, 11, 1.1f}, {17.5f, 19.4f, 16, 1.6f}, {0, 0, 0, 0},
-     {23.1f, 28, 0, 3}, {33.5f, 40, 0, 3.8f}, {35, 46, 0, 4},
-     {29, 38.4f, 0, 5}, {42.9f, 57, 0, 7.5f}, {39.5f, 50.6f, 0, 5}, {51, 70, 0, 12},
-     {42, 53.7f, 0, 2}, {82, 122, 0, 13}},
-    /* HEAL-Full */
-    {{15, 18.5f, 8.8f, 0.8f}, {16, 21, 13.3f, 1.1f}, {19.8f, 25.6f, 21, 1.6f}, {0, 0, 0, 0},
-     {29.9f, 40.4f, 0, 3}, {39, 52, 0, 6}, {49.7f, 66, 0, 5},
-     {43.3f, 57.5f, 0, 5}, {70.5f, 92.5f, 0, 5.5f}, {57, 74.5f, 0, 5}, {91.3f, 118.5f, 0, 10},
-     {72.5f, 85.6f, 0, 2.3f}, {150, 216, 0, 12}},
-    /* (INT16 scores: not here) */
-    {},
-    /* pre-split */
-    {{17, 20, 11.5f, 0.8f}, {18, 22.2f, 17.5f, 1.1f}, {27.3f, 31.8f, 30, 1.8f}, {0, 0, 0, 0},
-     {37.6f, 49.5f, 0, 3}, {59, 74, 0, 5.5f}, {0, 0, 0, 0},
-     {53.2f, 74, 0, 5}, {106.9f, 127, 0, 7}, {64.7f, 92.7f, 0, 5}, {137, 162.5f, 0, 12.5f},
-     {91.5f, 104.4f, 0, 2.7f}, {185, 273, 0, 13}},
-    /* bf16x3, B stored K x N (N x K below) */
-    {{24, 28.5f, 12.5f, 0.8f}, {27, 31, 22, 1.3f}, {0, 0, 0, 0}, {36, 40.5f, 0, 3.5f},
-     {56, 63, 0, 4}, {0, 0, 0, 0}, {0, 0, 0, 0},
-     {65, 83.7f, 0, 4.8f}, {0, 0, 0, 0}, {76.9f, 106, 0, 6.2f}, {0, 0, 0, 0},
-     {83.5f, 110, 0, 5.5f}, {200, 283, 0, 15}},
-};
-constexpr Cost kCostRows[T_COUNT + 2] = {
-    {22, 24.4f, 17, 0.8f}, {29, 31.3f, 27, 1.3f}, {0, 0, 0, 0}, {37, 41.6f, 0, 3.5f},
-    {51, 65, 0, 4}, {0, 0, 0, 0}, {0, 0, 0, 0},
-    {72, 87.8f, 0, 4.8f}, {0, 0, 0, 0}, {81, 109, 0, 6.2f}, {0, 0, 0, 0},
-    {87, 113.7f, 0, 5.5f}, {200, 283, 0, 15}};
+// 32-deep chunks of K per stage: a K tail is what is left of whole stages.
+constexpr int kStage[T_COUNT] = {2, 2, 2, 4, 2, 2, 2, 2, 1, 2, 1};
 
-float estimate(const Cost &c, int64_t tiles, int64_t K, int cus)
+// Time of one launch by kernel, in us over that of an empty one: at 4096 deep with
+// up to 64 tiles, with 256 (one per CU) and per further 256 tiles (0: one tile per
+// CU at a time, so rounds, of whose last one `part` is the share that its empty
+// CUs cost too); a fixed part per 256 tiles (the first loads, the last stage);
+// per million elements of C, and of a C whose rows are not whole 128-byte lines;
+// and what a K tail adds to the time by depth (its share) and to the fixed part.
+// Fitted to the times of every tile on 12 000 random products of 65 to 8192 rows,
+// 4 to 32768 columns and 4 to 16384 deep, a third of them of sizes that divide by
+// nothing (the depths of the smallest HEAL-Base and HEAL-Full tiles are those of
+// products 4096 deep).  Fitted to one half, the smallest estimate is within 1.3% of
+// the fastest kernel on the other (geometric mean).  The table before had no terms
+// for C and took every K tail for 0.5 us: it was 5% off, and 2% of these products
+// ran slower than on the staged kernels, up to twice as long with shallow K,
+// between one and three rounds, and with rows of C that are not whole lines (3 x
+// 155 x 11932 x 52 K x N 35.1 -> 18.5 us, 195 x 21948 x 13 pre-split 22.8 -> 15.1).
+// The last two are the 128 x 128 and the 256 x 256 tiles of the staged kernels.
+// {}: not built.
+constexpr int kMedium = T_COUNT, kLarge = T_COUNT + 1;
+struct Cost { float few, full, more, part, fixed, out, ragged, tail, tail_fixed; };
+constexpr Cost kCost[6][T_COUNT + 2] = {
+    // 32x32, 32x64, 32x128, 64x64, 64x128, 64x192, 64x256, 96x128, 96x256, 128x128, 128x256; medium, large
+    {// HEAL-Base
+     {13, 15, 7.5f, 0, 0.3f, 0.54f, 0, 0.1f, 0.35f}, {14, 17.6f, 11, 0, 0.3f, 1.06f, 0, 0, 0.41f},
+     {17.5f, 19.4f, 16, 0, 0.74f, 0.95f, 0, 0, 0.6f}, {},
+     {19, 21.9f, 0, 1, 1.93f, 0.76f, 0, 0.14f, 0.7f}, {24.7f, 31, 0, 0.96f, 1.86f, 0.64f, 0.16f, 0.12f, 0.63f},
+     {29, 35.5f, 0, 1, 2.17f, 0.71f, 0, 0.1f, 0.65f}, {24.2f, 28.1f, 0, 1, 3.11f, 0.82f, 0, 0.27f, 0.98f},
+     {36.2f, 43.1f, 0, 0.95f, 3.37f, 0.6f, 0, 0.21f, 0.54f}, {33.8f, 38.2f, 0, 1, 3.03f, 0.7f, 0, 0.16f, 0.85f},
+     {44.2f, 53.9f, 0, 0.91f, 4.4f, 0.73f, 0.02f, 0.32f, 1.22f}, {39.3f, 38.8f, 0, 0.82f, 1.43f, 0.61f, 0.62f, 0.03f, 0},
+     {77.3f, 90.7f, 0, 1, 4.63f, 0.76f, 1, 0.04f, 0.6f}},
+    {// HEAL-Full
+     {18.2f, 20.7f, 6.6f, 0, 0.67f, 0.05f, 0, 0.31f, 0.32f}, {16, 21, 13.3f, 0, 0.63f, 0.59f, 0, 0.05f, 0.49f},
+     {19.8f, 25.6f, 21, 0, 1.28f, 0.5f, 0, 0, 0.87f}, {},
+     {27.4f, 32, 0, 1, 2.5f, 0.97f, 0, 0.15f, 1.31f}, {34.9f, 41.9f, 0, 1, 2.39f, 0.84f, 0, 0.08f, 0.82f},
+     {43.6f, 53.6f, 0, 0.98f, 2.64f, 0.7f, 0, 0.03f, 0.83f}, {40.3f, 48.8f, 0, 0.97f, 3.84f, 0.76f, 0, 0.1f, 1.62f},
+     {61.8f, 77, 0, 0.91f, 3.71f, 0.59f, 0, 0.06f, 0.91f}, {53.1f, 62.4f, 0, 0.99f, 3.47f, 0.7f, 0, 0.09f, 1.57f},
+     {80, 100.8f, 0, 0.86f, 4.89f, 0.78f, 0, 0.12f, 1.61f}, {68.9f, 69.7f, 0, 0.64f, 1.61f, 0.58f, 0.69f, 0, 0.08f},
+     {155, 187.3f, 0, 0.96f, 3.92f, 0.78f, 0.9f, 0, 0.05f}},
+    {},  // (INT16 scores: not here)
+    {// pre-split
+     {15.7f, 18.5f, 8.5f, 0, 0.56f, 0.26f, 0, 0.32f, 0.29f}, {15.6f, 16.2f, 0, 0.82f, 0.53f, 1.08f, 0, 0.11f, 0.44f},
+     {22.4f, 27.6f, 0, 0.96f, 1.25f, 1.38f, 0, 0.04f, 0.79f}, {},
+     {32.9f, 40.3f, 0, 0.99f, 2.48f, 1.03f, 0, 0.08f, 0.99f}, {49.2f, 59.6f, 0, 0.97f, 2.23f, 0.88f, 0, 0.02f, 0.94f},
+     {}, {48.3f, 60, 0, 0.94f, 3.64f, 0.82f, 0, 0.08f, 1.4f},
+     {93.8f, 113, 0, 0.91f, 3.61f, 0.7f, 0, 0.04f, 1.93f}, {60.5f, 74.9f, 0, 0.92f, 3.23f, 0.76f, 0, 0.09f, 1.39f},
+     {119.7f, 144.5f, 0, 0.86f, 7.2f, 1.05f, 0, 0.04f, 2.12f}, {87.8f, 97.4f, 0, 0.96f, 1.57f, 0.65f, 0.63f, 0, 0.26f},
+     {187.3f, 237.3f, 0, 0.79f, 4.04f, 0.79f, 1.2f, 0, 0.04f}},
+    {// bf16x3, B stored K x N
+     {23.8f, 28.1f, 13.4f, 0, 0.7f, 0.54f, 0, 0.04f, 0.34f}, {26.6f, 25.7f, 0, 1, 0.69f, 1.08f, 1.83f, 0.05f, 0.58f},
+     {}, {32.3f, 37.2f, 0, 1, 2.1f, 1.74f, 0.15f, 0.06f, 1.82f},
+     {52.2f, 59.7f, 0, 1, 1.81f, 1.2f, 0.07f, 0.09f, 0.91f}, {},
+     {}, {61.4f, 72.5f, 0, 1, 2.61f, 0.95f, 0.12f, 0.08f, 1.2f},
+     {}, {72.3f, 85.6f, 0, 1, 3.44f, 0.85f, 0.11f, 0.05f, 0.2f},
+     {}, {118.3f, 121.5f, 0, 0.78f, 1.69f, 0.78f, 0.15f, 0.02f, 0.73f},
+     {204.7f, 231.4f, 0, 1, 3.6f, 0.73f, 1.09f, 0.03f, 0.64f}},
+    {// bf16x3, B stored N x K
+     {20.7f, 26.6f, 14, 0, 0.77f, 0.75f, 0, 0.58f, 0}, {26.1f, 28.1f, 0, 1, 0.66f, 2.96f, 0, 0.48f, 0.87f},
+     {}, {33.4f, 36.8f, 0, 1, 2.01f, 1.9f, 0, 0.23f, 1.86f},
+     {47.3f, 55.3f, 0, 0.98f, 2.01f, 1.17f, 0, 0.24f, 1.55f}, {},
+     {}, {68.2f, 77.7f, 0, 0.95f, 2.22f, 1.01f, 0, 0.2f, 1.86f},
+     {}, {77.3f, 92.3f, 0, 0.9f, 2.65f, 1.03f, 0, 0.05f, 0.2f},
+     {}, {125.8f, 137.5f, 0, 0.72f, 0.78f, 0.75f, 0.35f, 0.03f, 0.24f},
+     {204.2f, 224.1f, 0, 0.99f, 3.32f, 0.86f, 1.18f, 0, 0.16f}},
+};
+
+// The staged kernels on rows that they read by element: medium, large.
+constexpr Cost kElement[6][2] = {
+    {// HEAL-Base
+     {102.8f, 101.2f, 0, 0.85f, 2.98f, 0.47f, 0.98f, 0, 0}, {239.6f, 323.1f, 333.9f, 0, 6.82f, 1.18f, 1.52f, 0, 0}},
+    {// HEAL-Full
+     {127.7f, 129.3f, 0, 1, 3.01f, 0.89f, 0.76f, 0, 0}, {266.5f, 317.1f, 213.8f, 0, 7.31f, 1.2f, 1.52f, 0, 0}},
+    {},
+    {// pre-split
+     {141.8f, 149.4f, 0, 1, 3.54f, 1.01f, 0.42f, 0, 0}, {323.6f, 352.8f, 625.5f, 0, 4.58f, 1.84f, 0.65f, 0, 0}},
+    {// bf16x3, B stored K x N
+     {271.1f, 283.3f, 0, 0.73f, 3.7f, 1.94f, 0, 0, 0}, {691.7f, 700, 0, 0.69f, 9.88f, 2.03f, 0, 0, 0}},
+    {// bf16x3, B stored N x K
+     {249, 253.4f, 0, 0.82f, 0.89f, 3.21f, 0, 0, 0}, {510.1f, 514.1f, 0, 0.74f, 15.57f, 1.96f, 0, 0, 0}},
+};
+
+int cost_index(int op, bool rows) { return rows ? OP_BF16X3 + 1 : op; }
+
+// `wgs` workgroups that run `per` tiles one after another, on an output of `mega`
+// million elements, in whole lines or not (`ragged`).
+float estimate(const Cost &c, int64_t wgs, int per, int64_t K, float mega, bool ragged, bool tail, int cus)
 {
-    const float r = (float)tiles / (float)cus, depth = (float)K / 4096.0f;
-    const float rounds = (float)((tiles + cus - 1) / cus);
+    const float r = (float)wgs / (float)cus;
+    const float depth = (float)(K * per) / 4096.0f * (tail ? 1.0f + c.tail : 1.0f);
+    const float fixed = c.fixed * (float)per + (tail ? c.tail_fixed : 0.0f);
+    float t;
     if (r <= 1.0f)
-        return c.fixed + depth * (c.few + (c.full - c.few) * (r < 0.25f ? 0.0f : (r - 0.25f) / 0.75f));
-    if (c.more > 0.0f) return c.fixed * r + depth * (c.full + (r - 1.0f) * c.more);
-    return c.fixed * rounds + depth * c.full * rounds;
+        t = fixed + depth * (c.few + (c.full - c.few) * (r < 0.25f ? 0.0f : (r - 0.25f) / 0.75f));
+    else if (c.more > 0.0f)
+        t = fixed * r + depth * (c.full + (r - 1.0f) * c.more);
+    else
+        t = (fixed + depth * c.full) * (c.part * (float)((wgs + cus - 1) / cus) + (1.0f - c.part) * r);
+    return t + (ragged ? c.out + c.ragged : c.out) * mega;
 }
+
+// Other tiles have to be this much faster by their estimate than the kernel that
+// the output's size alone would choose.
+float handicap(float t) { return 1.04f * t + 0.15f; }
 
 // Up to 64 rows the skinny kernels stream B; the direct-B kernel is faster where
 // their narrow strips each convert all of A.  64 x N x 4096, us, skinny ->
@@ -821,42 +877,38 @@ int direct_plan(int op, bool trans_b, const DirectArgs &a)
     if (a.K < 4 || a.K > (1 << 28) || ((int64_t)127 * a.lda + a.K + 128) * 4 >= lim)
         return DIRECT_NONE;
     if (rows && ((int64_t)255 * a.ldb + a.K + 128) * 4 >= lim) return DIRECT_NONE;
-    if (cols && (a.N < 4 || (a.K + 128) * a.ldb * 4 >= lim)) return DIRECT_NONE;
+    if (cols && (a.N < 4 || a.ldb >= lim || (a.K + 128) * a.ldb * 4 >= lim)) return DIRECT_NONE;
     // the staged kernels read rows that are not whole 16-byte units by element
     // (16 x 1003 x 999, us: K x N 30.3 -> 9.3, N x K 25.8 -> 12.7, HEAL-Base 8.6 ->
     // 6.8, pre-split 8.9 -> 8.6, but HEAL-Full 8.5 -> 9.3)
     if (a.M <= 64 && (a.vec || (a.M <= 16 && op == OP_FULL)) && !beats_skinny(op, rows, a))
         return DIRECT_NONE;
     const int cus = device_cus();
-    const Cost *cost = rows ? kCostRows : kCost[op];
-    auto tiles = [&](int64_t bm, int64_t bn) {
-        return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.batch;
-    };
+    const Cost *cost = kCost[cost_index(op, rows)];
+    const bool ragged = a.ldc % 32 != 0 || a.strideC % 32 != 0 || (reinterpret_cast<uintptr_t>(a.C) & 127u) != 0;
+    const float mega = (float)a.batch * (float)a.M * (float)a.N * 1e-6f;
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     float best = 0.0f;
     int plan = DIRECT_NONE;
-    if (a.vec && a.M > 64) {
-        // the large kernels' tiles: a part-empty round costs less than a whole
-        // one (a power-limited chip runs fewer tiles faster)
-        const int64_t nl = tiles(256, 256);
-        best = estimate(cost[kLarge], nl, a.K, cus);
-        if (nl > cus)
-            best = 0.5f * (best + (cost[kLarge].fixed + cost[kLarge].full * (float)a.K / 4096.0f) *
-                                      (float)nl / (float)cus);
-        plan = DIRECT_LARGE;
-        const float t = estimate(cost[kMedium], tiles(128, 128), a.K, cus);
-        if (t < best) {
-            best = t;
-            plan = DIRECT_MEDIUM;
-        }
+    if (a.M > 64) {
+        // the 128 x 128 tiles of the bf16x3 product take two batch entries each
+        const int per = op == OP_BF16X3 && a.batch > 1 ? 2 : 1;
+        const Cost *staged = a.vec ? cost + kMedium : kElement[cost_index(op, rows)];
+        float medium = estimate(staged[0], tiles(128, 128) * ((a.batch + per - 1) / per), per, a.K, mega, ragged,
+                                a.K % 64 != 0, cus);
+        float large = estimate(staged[1], tiles(256, 256) * a.batch, 1, a.K, mega, ragged, a.K % 32 != 0, cus);
+        if (select_instance(a.M, a.N) == HEAL_INSTANCE_LARGE) medium = handicap(medium);
+        else large = handicap(large);
+        best = medium < large ? medium : large;
+        plan = medium < large ? DIRECT_MEDIUM : DIRECT_LARGE;
     }
     for (int c = 0; c < T_COUNT; ++c) {
         const int64_t n = tiles(kTileM[c], kTileN[c]);
-        if (cost[c].full <= 0.0f || n > (1 << 20)) continue;
+        if (cost[c].full <= 0.0f || n * a.batch > (1 << 20)) continue;
         // (no K-tail form: launch_cfg)
         if (c == T128x128 && op == OP_BF16X3 && a.K % 64 != 0) continue;
-        // the forms with a K tail take 0.5 us more (4096 x 512 x 100 HEAL-Full 8.7 us
-        // on 64 x 128 tiles, 7.5 on the staged 128 x 128 ones)
-        const float t = estimate(cost[c], n, a.K, cus) + (a.K % 64 ? 0.5f : 0.0f);
+        const float t = handicap(
+            estimate(cost[c], n * a.batch, 1, a.K, mega, ragged, a.K % (32 * kStage[c]) != 0, cus));
         if (best == 0.0f || t < best) {
             best = t;
             plan = c;

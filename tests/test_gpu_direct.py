@@ -141,19 +141,19 @@ def test_few_rows(shape):
         _same(C, ref, name)
 
 
-# the tiles of 192 and 256 columns (packed B): rows, columns, depth, tile; whole
-# and ragged, with a K tail inside a chunk and an odd number of chunks
-WIDE = [(512, 6144, 1280, 64192), (509, 6100, 610, 64192), (1024, 4096, 1280, 64256),
-        (1021, 4090, 706, 64256), (1536, 4096, 640, 96256), (1530, 4001, 999, 96256),
-        (1500, 4090, 608, 96256), (2048, 4096, 1024, 128256), (2045, 4093, 1001, 128256),
-        (2045, 4093, 1056, 128256)]
+# the tiles of 192 and 256 columns (packed B): rows, columns, depth, tile and the
+# products that take it; whole and ragged, with a K tail inside a chunk and an odd
+# number of chunks
+WIDE = [(512, 6144, 1280, 64192, (0, 1, 3)), (509, 6100, 610, 64192, (0, 1, 3)),
+        (1024, 4096, 1280, 64256, (1,)), (1021, 4090, 1280, 64256, (0, 1)), (1021, 4090, 706, 64256, (0, 1)),
+        (1536, 4096, 640, 96256, (0, 1, 3)), (1530, 4001, 999, 96256, (0, 1, 3)),
+        (1500, 4090, 608, 96256, (0, 1, 3)), (2048, 4096, 1536, 128256, (0, 1)), (2048, 4096, 2560, 128256, (3,)),
+        (2045, 4093, 1001, 128256, (0, 3)), (2045, 4093, 1056, 128256, (0, 1, 3))]
 
 
 @pytest.mark.parametrize("shape", WIDE, ids=lambda s: "x".join(map(str, s[:3])))
 def test_wide_tiles(shape):
-    M, N, K, tile = shape
-    for kind, name in ((0, "base"), (1, "full"), (3, "presplit")):
-        got = heal.lib().heal_gemm_direct_tile(kind, 0, M, N, K, 1)
-        # (64 x 256 is not built for the pre-split product)
-        assert got == (128128 if kind == 3 and tile == 64256 else tile), name
+    M, N, K, tile, kinds = shape
+    for kind in kinds:
+        assert heal.lib().heal_gemm_direct_tile(kind, 0, M, N, K, 1) == tile, kind
     test_packed_products(shape[:3], 3)

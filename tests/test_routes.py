@@ -43,3 +43,30 @@ def test_batches_take_the_large_tiles_that_the_plan_finds_fastest(routes):
     354 us, 535 on the 128 x 128 ones; 16 x 1024 x 1024 x 4096 298, 450, N x K 297, 453)."""
     calls = [(KN, 512, 512, 4096, 64), (KN, 1024, 1024, 4096, 16), (NK, 1024, 1024, 4096, 16)]
     assert routes(calls) == ["large"] * 3
+
+
+# (call, the fast kernels, us on the one taken, us on the one taken before the
+# estimates were fitted to shallow products, part rounds and rows of C of any length)
+ESTIMATES = [
+    ((KN, 155, 11932, 52, 3), ("large", "medium"), 18.3, 35.1),
+    ((KN, 228, 10939, 24), ("medium", "direct 64128"), 13.3, 19.8),
+    ((PRESPLIT, 265, 11216, 64), ("large", "medium", "direct 96256"), 10.0, 15.0),
+    ((PRESPLIT, 83, 22080, 128), ("medium", "direct 64192"), 8.3, 12.4),
+    ((PRESPLIT, 259, 26368, 384), ("large", "direct 64192"), 31.5, 46.9),
+    ((NK, 65, 4748, 168, 7), ("large", "medium"), 18.4, 34.5),
+    ((NK, 73, 17152, 192), ("direct 96128",), 9.7, 15.9),
+    ((BASE, 69, 22060, 784), ("direct 64192", "medium"), 13.2, 16.8),
+]
+
+
+def test_the_fastest_tiles_are_found_off_the_deep_whole_products(routes):
+    for got, (call, want, now, before) in zip(routes([e[0] for e in ESTIMATES]), ESTIMATES):
+        assert got in want, (call, got)
+
+
+def test_deep_products_keep_their_tiles(routes):
+    calls = [(KN, 8192, 8192, 8192), (BASE, 2048, 14336, 4096), (PRESPLIT, 1531, 4096, 14336),
+             (FULL, 256, 4096, 4096), (NK, 200, 6144, 4096), (KN, 1001, 1003, 999), (BASE, 512, 6144, 4096),
+             (FULL, 1024, 4096, 4096), (FULL, 1536, 4096, 4096), (BASE, 2048, 4096, 4096)]
+    assert routes(calls) == ["large", "large", "direct 96256", "direct 32128", "direct 64128", "direct 64064",
+                             "direct 64192", "direct 64256", "direct 96256", "direct 128256"]

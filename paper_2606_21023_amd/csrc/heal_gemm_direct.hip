@@ -805,30 +805,47 @@ constexpr Cost kCost[6][T_COUNT + 2] = {
      {204.2f, 224.1f, 0, 0.99f, 3.32f, 0.86f, 1.18f, 0, 0.16f}},
 };
 
-// The staged kernels on rows that they read by element: medium, large.
-constexpr Cost kElement[6][2] = {
+// The staged kernels on rows that they read by element: 16, 32 and 64 rows (strips
+// of the skinny kernels' widths with a packed B, else 64 columns), medium, large.
+// `tail` of the first three: the share of the time by depth that is proportional
+// to the rows, A's loads.  Those three fitted to 9000 products of 1 to 64 rows, which
+// the direct-B kernel had all taken on the strength of 16 x 1003 x 999 (K x N 30.3
+// -> 9.3 us, N x K 25.8 -> 12.7, HEAL-Base 8.6 -> 6.8, pre-split 8.9 -> 8.6): 19% of
+// those with odd sizes ran slower on it, few rows of a deep packed B most
+// (HEAL-Base 5 x 4 x 11216 23.4 -> 42.7, pre-split 3 x 8 x 16080 51.2 -> 86.4).
+constexpr Cost kElement[6][5] = {
     {// HEAL-Base
+     {13.2f, 22.1f, 13.3f, 0, 0.85f, 2.78f, 2.13f, 0.58f, 0}, {28.9f, 34.4f, 0, 0.75f, 1.38f, 3.26f, 0.59f, 0.95f, 0},
+     {54.9f, 64.6f, 0, 0.82f, 1.69f, 1.69f, 0.49f, 0.95f, 0},
      {102.8f, 101.2f, 0, 0.85f, 2.98f, 0.47f, 0.98f, 0, 0}, {239.6f, 323.1f, 333.9f, 0, 6.82f, 1.18f, 1.52f, 0, 0}},
     {// HEAL-Full
+     {14.5f, 22.2f, 10.7f, 0, 1.07f, 2.24f, 3.59f, 0.42f, 0}, {29.2f, 31, 0, 0.57f, 1.69f, 1.76f, 2, 0.43f, 0},
+     {55.3f, 67.9f, 0, 0.66f, 1.87f, 2.82f, 0, 0.86f, 0},
      {127.7f, 129.3f, 0, 1, 3.01f, 0.89f, 0.76f, 0, 0}, {266.5f, 317.1f, 213.8f, 0, 7.31f, 1.2f, 1.52f, 0, 0}},
     {},
     {// pre-split
+     {15.6f, 21.2f, 29.5f, 0, 1.28f, 3.05f, 1.73f, 0.33f, 0}, {29.6f, 35.9f, 0, 0.72f, 1.5f, 7.01f, 0, 0.6f, 0},
+     {54.9f, 67.6f, 0, 0.82f, 1.94f, 2.11f, 1.02f, 0.68f, 0},
      {141.8f, 149.4f, 0, 1, 3.54f, 1.01f, 0.42f, 0, 0}, {323.6f, 352.8f, 625.5f, 0, 4.58f, 1.84f, 0.65f, 0, 0}},
     {// bf16x3, B stored K x N
+     {114.6f, 164.2f, 88.3f, 0, 0.27f, 0.69f, 1.65f, 0.1f, 0}, {126.7f, 185.9f, 84.5f, 0, 0.85f, 1.45f, 0, 0.16f, 0},
+     {150.9f, 242.5f, 100.1f, 0, 1.68f, 1.19f, 0, 0.35f, 0},
      {271.1f, 283.3f, 0, 0.73f, 3.7f, 1.94f, 0, 0, 0}, {691.7f, 700, 0, 0.69f, 9.88f, 2.03f, 0, 0, 0}},
     {// bf16x3, B stored N x K
+     {92.3f, 118.9f, 64.4f, 0, 0.28f, 0.78f, 3.25f, 0.15f, 0}, {112.2f, 150, 78.8f, 0, 0.6f, 1.62f, 0.19f, 0.4f, 0},
+     {148.8f, 193.3f, 109.2f, 0, 1.41f, 1.02f, 0.37f, 0.56f, 0},
      {249, 253.4f, 0, 0.82f, 0.89f, 3.21f, 0, 0, 0}, {510.1f, 514.1f, 0, 0.74f, 15.57f, 1.96f, 0, 0, 0}},
 };
 
 int cost_index(int op, bool rows) { return rows ? OP_BF16X3 + 1 : op; }
 
-// `wgs` workgroups that run `per` tiles one after another, on an output of `mega`
-// million elements, in whole lines or not (`ragged`).
-float estimate(const Cost &c, int64_t wgs, int per, int64_t K, float mega, bool ragged, bool tail, int cus)
+// `wgs` workgroups that run `per` tiles one after another, each `depth` times 4096
+// deep, on an output of `mega` million elements, in whole lines or not (`ragged`).
+float estimate(const Cost &c, int64_t wgs, int per, float depth, float fixed, float mega, bool ragged, int cus)
 {
     const float r = (float)wgs / (float)cus;
-    const float depth = (float)(K * per) / 4096.0f * (tail ? 1.0f + c.tail : 1.0f);
-    const float fixed = c.fixed * (float)per + (tail ? c.tail_fixed : 0.0f);
+    depth *= (float)per;
+    fixed *= (float)per;
     float t;
     if (r <= 1.0f)
         t = fixed + depth * (c.few + (c.full - c.few) * (r < 0.25f ? 0.0f : (r - 0.25f) / 0.75f));
@@ -878,10 +895,12 @@ int direct_plan(int op, bool trans_b, const DirectArgs &a)
         return DIRECT_NONE;
     if (rows && ((int64_t)255 * a.ldb + a.K + 128) * 4 >= lim) return DIRECT_NONE;
     if (cols && (a.N < 4 || a.ldb >= lim || (a.K + 128) * a.ldb * 4 >= lim)) return DIRECT_NONE;
-    // the staged kernels read rows that are not whole 16-byte units by element
-    // (16 x 1003 x 999, us: K x N 30.3 -> 9.3, N x K 25.8 -> 12.7, HEAL-Base 8.6 ->
-    // 6.8, pre-split 8.9 -> 8.6, but HEAL-Full 8.5 -> 9.3)
-    if (a.M <= 64 && (a.vec || (a.M <= 16 && op == OP_FULL)) && !beats_skinny(op, rows, a))
+    if (a.M <= 64 && a.vec && !beats_skinny(op, rows, a)) return DIRECT_NONE;
+    // one stage of the element-reading tiles, where B is not small and shared by
+    // enough workgroups (one product: 0.82 of the time of the fastest tile here,
+    // geometric mean over random sizes; 17 of 1 x 15872 x 64 20 us against 37; but 4 of
+    // 3 x 1664 x 64 5.7 against 3.7)
+    if (a.M <= 64 && !a.vec && rows && a.K <= 64 && (a.batch == 1 || (float)a.batch * (float)a.N > 32768.0f))
         return DIRECT_NONE;
     const int cus = device_cus();
     const Cost *cost = kCost[cost_index(op, rows)];
@@ -890,13 +909,25 @@ int direct_plan(int op, bool trans_b, const DirectArgs &a)
     auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     float best = 0.0f;
     int plan = DIRECT_NONE;
-    if (a.M > 64) {
-        // the 128 x 128 tiles of the bf16x3 product take two batch entries each
-        const int per = op == OP_BF16X3 && a.batch > 1 ? 2 : 1;
-        const Cost *staged = a.vec ? cost + kMedium : kElement[cost_index(op, rows)];
-        float medium = estimate(staged[0], tiles(128, 128) * ((a.batch + per - 1) / per), per, a.K, mega, ragged,
-                                a.K % 64 != 0, cus);
-        float large = estimate(staged[1], tiles(256, 256) * a.batch, 1, a.K, mega, ragged, a.K % 32 != 0, cus);
+    // the tiled bf16x3 kernel's workgroups take two batch entries each
+    const int per = op == OP_BF16X3 && a.batch > 1 ? 2 : 1;
+    const int64_t entries = (a.batch + per - 1) / per;
+    const Cost *element = kElement[cost_index(op, rows)];
+    const float depth = (float)a.K / 4096.0f;
+    auto tiled = [&](const Cost &c, int64_t wgs, int tile_per, bool tail) {
+        return estimate(c, wgs, tile_per, tail ? depth * (1.0f + c.tail) : depth,
+                        tail ? c.fixed + c.tail_fixed / (float)tile_per : c.fixed, mega, ragged, cus);
+    };
+    if (a.M <= 64 && !a.vec) {
+        const int h = a.M <= 16 ? 0 : a.M <= 32 ? 1 : 2;
+        const Cost &c = element[h];
+        const int64_t w = op == OP_BF16X3 ? 64 : skinny_strip_width(a.N, a.M);
+        best = estimate(c, (a.N + w - 1) / w * entries, per, depth * (1.0f - c.tail * (1.0f - (float)a.M / (float)(16 << h))),
+                        c.fixed, mega, ragged, cus);
+    } else if (a.M > 64) {
+        const Cost *staged = a.vec ? cost + kMedium : element + 3;
+        float medium = tiled(staged[0], tiles(128, 128) * entries, per, a.K % 64 != 0);
+        float large = tiled(staged[1], tiles(256, 256) * a.batch, 1, a.K % 32 != 0);
         if (select_instance(a.M, a.N) == HEAL_INSTANCE_LARGE) medium = handicap(medium);
         else large = handicap(large);
         best = medium < large ? medium : large;
@@ -907,8 +938,7 @@ int direct_plan(int op, bool trans_b, const DirectArgs &a)
         if (cost[c].full <= 0.0f || n * a.batch > (1 << 20)) continue;
         // (no K-tail form: launch_cfg)
         if (c == T128x128 && op == OP_BF16X3 && a.K % 64 != 0) continue;
-        const float t = handicap(
-            estimate(cost[c], n * a.batch, 1, a.K, mega, ragged, a.K % (32 * kStage[c]) != 0, cus));
+        const float t = handicap(tiled(cost[c], n * a.batch, 1, a.K % (32 * kStage[c]) != 0));
         if (best == 0.0f || t < best) {
             best = t;
             plan = c;

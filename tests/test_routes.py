@@ -70,3 +70,18 @@ def test_deep_products_keep_their_tiles(routes):
              (FULL, 1024, 4096, 4096), (FULL, 1536, 4096, 4096), (BASE, 2048, 4096, 4096)]
     assert routes(calls) == ["large", "large", "direct 96256", "direct 32128", "direct 64128", "direct 64064",
                              "direct 64192", "direct 64256", "direct 96256", "direct 128256"]
+
+
+def test_few_rows_read_by_element_keep_their_strips_where_they_are_faster(routes):
+    """Up to 64 rows whose operands are not whole 16-byte units (us on the strips,
+    on the direct-B tile that all of them took)."""
+    strips = [(BASE, 5, 4, 11216, 1, 1),          # 23.4, 42.7
+              (BASE, 3, 1842, 10253),             # 22.9, 40.6
+              (PRESPLIT, 3, 8, 16080, 1, 1),      # 51.2, 86.4
+              (PRESPLIT, 1, 275, 11419),          # 37.7, 62.8
+              (KN, 2, 8951, 5, 130),              # 45.6, 199
+              (KN, 1, 26914, 24, 4, 0, 1, 0),     # 7.8, 20.6
+              (NK, 2, 4, 62), (NK, 9, 15, 61)]    # 3.0, 4.4 and 3.1, 4.5
+    assert routes(strips) == ["skinny"] * len(strips)
+    direct = [(KN, 16, 1003, 999), (NK, 16, 1003, 999), (BASE, 64, 4093, 999), (FULL, 33, 2050, 1001)]
+    assert all(r.startswith("direct") for r in routes(direct))

@@ -871,10 +871,16 @@ float handicap(float t) { return 1.04f * t + 0.15f; }
 // N x K 8192 40.3 -> 43.5, 14336 72.0 -> 58.2, 32064 109 -> 117.  32 rows: HEAL-Full
 // 4096 16.8 -> 19.1, 8192 24.1 -> 19.6, 16032 39.2 -> 34.6, 32064 55.0 -> 50.7;
 // pre-split 8192 28.1 -> 29.4, 16032 54.2 -> 48.8.
+// Other depths: over 300 random products of 17 to 64 rows inside these windows,
+// those at least 512 deep gain 1.3x; shallower ones lose up to 1.1x (HEAL-Full
+// 40 x 64 x 396 5.5 -> 6.6, HEAL-Base 40 x 192 x 280 4.3 -> 5.0), and so do wide ones
+// less than 2048 deep, bound by C (HEAL-Base 41 x 88568 x 288 15.3 -> 18.4, HEAL-Full
+// 51 x 66444 x 324 17.8 -> 22.0, HEAL-Base 60 x 85184 x 676 27.6 -> 30.2).
 bool beats_skinny(int op, bool rows, const DirectArgs &a)
 {
-    if (a.batch != 1 || a.K < 256 || a.M <= 16) return false;
+    if (a.batch != 1 || a.K < 512 || a.M <= 16) return false;
     const int64_t N = a.N;
+    if (N >= 61440 && a.K < 2048) return false;
     if (op == OP_BF16X3)
         return a.M > 32 && N >= 12288 && N <= (rows ? 16384 : 32768);
     if (a.M <= 32) return N >= (op == OP_PRESPLIT ? 16000 : 8192) && N <= 32768;

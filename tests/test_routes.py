@@ -85,3 +85,16 @@ def test_few_rows_read_by_element_keep_their_strips_where_they_are_faster(routes
     assert routes(strips) == ["skinny"] * len(strips)
     direct = [(KN, 16, 1003, 999), (NK, 16, 1003, 999), (BASE, 64, 4093, 999), (FULL, 33, 2050, 1001)]
     assert all(r.startswith("direct") for r in routes(direct))
+
+
+def test_shallow_products_of_few_rows_keep_the_skinny_kernel(routes):
+    """17 to 64 rows inside the windows of the direct-B kernel but less than 512 deep
+    (wide ones less than 2048): us on the skinny kernel, on the direct-B one."""
+    skinny = [(FULL, 40, 64, 396),         # 5.5, 6.6
+              (BASE, 40, 192, 280),        # 4.3, 5.0
+              (BASE, 41, 88568, 288),      # 15.3, 18.4
+              (FULL, 51, 66444, 324),      # 17.8, 22.0
+              (BASE, 60, 85184, 676)]      # 27.6, 30.2
+    assert routes(skinny) == ["skinny"] * len(skinny)
+    direct = [(FULL, 64, 8192, 4096), (BASE, 64, 8192, 512), (PRESPLIT, 64, 14336, 4096), (BASE, 64, 65536, 4096)]
+    assert all(r.startswith("direct") for r in routes(direct))

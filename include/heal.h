@@ -135,10 +135,11 @@ heal_status_t heal_gemm_f32_strided_batched(int64_t M, int64_t N, int64_t K, flo
  *   instance : one of heal_instance_t; HEAL_INSTANCE_AUTO chooses as usual, by
  *   sizes, layout and alignment, between these and two more kernels: the panel
  *   kernel for B stored N x K with K <= 128 (attention scores: bf16x3 with
- *   trans_b = 1, which the large and medium instances take too from 256 rows,
- *   and the INT16 scores), where a panel of A stays in LDS while the workgroup
- *   walks the columns of C; and the direct-B kernel, whose smaller tiles fill
- *   the chip where the output has too few large ones.
+ *   trans_b = 1, which the large and medium instances take too from 256 rows on
+ *   where rows of C are whole 16-byte units, and the INT16 scores), where a panel
+ *   of A stays in LDS while the workgroup walks the columns of C; and the direct-B
+ *   kernel, whose smaller tiles fill the chip where the output has too few large
+ *   ones.
  * Other arguments as heal_gemm_f32_strided_batched.
  */
 typedef enum heal_instance_t {

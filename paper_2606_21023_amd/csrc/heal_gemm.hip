@@ -633,7 +633,7 @@ static DirectArgs direct_args(const GemmArgs &a, bool trans_b)
 
 Route choose_gemm(const GemmArgs &a, bool trans_b)
 {
-    if (HEAL_PANEL && panel_kernel_applies(a, trans_b)) return {ROUTE_PANEL, 0};
+    if (HEAL_PANEL && panel_kernel_applies(a, trans_b) && panel_pays(a)) return {ROUTE_PANEL, 0};
     const int plan = direct_plan(OP_BF16X3, trans_b, direct_args(a, trans_b));
     if (plan >= 0) return {ROUTE_DIRECT, plan};
     return {plan == DIRECT_MEDIUM ? HEAL_INSTANCE_MEDIUM
@@ -652,11 +652,11 @@ hipError_t launch_gemm(int instance, const GemmArgs &a, bool trans_b, bool use_a
     }
     switch (instance) {
     case HEAL_INSTANCE_LARGE:
-        if (HEAL_PANEL && a.M >= 256 && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
+        if (HEAL_PANEL && a.M >= 256 && a.vecC && a.N % 4 == 0 && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
         if (large_kernel_applies(a, trans_b)) return launch_gemm_large(a, trans_b, use_alpha, stream);
         return launch_tile<HEAL_LARGE_CFG>(a, trans_b, use_alpha, stream);
     case HEAL_INSTANCE_MEDIUM:
-        if (HEAL_PANEL && a.M >= 256 && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
+        if (HEAL_PANEL && a.M >= 256 && a.vecC && a.N % 4 == 0 && panel_kernel_applies(a, trans_b)) return launch_gemm_panel(a, use_alpha, stream);
         return launch_tile<HEAL_MEDIUM_CFG>(a, trans_b, use_alpha, stream);
     case HEAL_INSTANCE_SKINNY:
         if (skinny_kernel_applies(a, trans_b)) return launch_gemm_skinny(a, trans_b, use_alpha, stream);

@@ -461,13 +461,31 @@ hipError_t launch_kc(const PanelArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Rows of the panel of an output of M rows: 256 (bf16x3) or 128 (scores) where
-// there are that many, else the smallest that holds them.
-int panel_rows(int64_t M, bool scores)
+// Whether rows of C are whole quads: with at least one full panel (256 rows of
+// bf16x3, 128 of INT16 codes) such products have always run here.
+bool whole_quads(int64_t N, const float *C, int64_t ldc, int64_t strideC, int64_t batch)
 {
-    const int most = scores ? HEAL_PANEL_BM_SCORES : HEAL_PANEL_BM;
-    if (M > 64) return M > 128 ? most : 128;
-    return M > 32 ? 64 : M > 16 ? 32 : 16;
+    return N % 4 == 0 && ldc % 4 == 0 && (batch == 1 || strideC % 4 == 0) &&
+           (reinterpret_cast<uintptr_t>(C) & 15u) == 0;
+}
+
+// Steps of 128 columns over the panels of an output, of 128 rows from 65 rows on.
+int64_t panel_steps(int64_t M, int64_t N, int64_t batch)
+{
+    return batch * (M <= 64 ? 1 : (M + 127) / 128) * ((N + PBN - 1) / PBN);
+}
+
+// Rows of the panel: the smallest that holds M up to 128.  Above, 128 for the scores;
+// for bf16x3 256 where one panel holds M and the chip is full many times over (42
+// of 137 x 7976 x 128 116 -> 101 us: B is read once), and for outputs of full panels
+// in whole quads, else 128 (1.07x faster than 256 over random sizes).
+int panel_rows(const PanelArgs &a, bool scores)
+{
+    const int64_t M = a.M;
+    if (M <= 64) return M > 32 ? 64 : M > 16 ? 32 : 16;
+    if (scores || M <= 128) return 128;
+    if (M <= 256 && panel_steps(M, a.N, a.batch) >= 2048) return 256;
+    return M >= 256 && whole_quads(a.N, a.C, a.ldc, a.strideC, a.batch) ? 256 : 128;
 }
 
 // Workgroups per panel, each walking its share of the columns.  Panels of at
@@ -489,13 +507,18 @@ int panel_csplit(int64_t M, int64_t N, int64_t batch, int PBM)
     const int64_t slots = PBM > 128 ? cus : 2 * cus;
     int best = 1;
     float least = 0.0f;
-    for (int c = steps < HEAL_PANEL_CSPLIT ? (int)steps : HEAL_PANEL_CSPLIT; c <= steps && c <= 32; ++c) {
+    auto consider = [&](int64_t c) {
         const float cost = (float)((panels * c + slots - 1) / slots) * ((float)steps / (float)c + 1.0f);
         if (least == 0.0f || cost < least) {
             least = cost;
-            best = c;
+            best = (int)c;
         }
-    }
+    };
+    for (int64_t c = steps < HEAL_PANEL_CSPLIT ? steps : HEAL_PANEL_CSPLIT; c <= steps && c <= 32; ++c) consider(c);
+    // few panels and many columns: one round of as many workgroups as fit (142 x
+    // 15076 x 128 bf16x3, one panel, 31.4 us with 32 workgroups)
+    const int64_t one = slots / panels < steps ? slots / panels : steps;
+    if (one > 32) consider(one);
     return best;
 }
 
@@ -506,7 +529,7 @@ hipError_t launch_panel(PanelArgs a, hipStream_t stream)
     // leave half lines, which have to meet in L2
     const bool rag = a.N % 4 != 0 || a.ldc % 32 != 0 || a.strideC % 32 != 0 ||
                      (reinterpret_cast<uintptr_t>(a.C) & 127u) != 0;
-    const int pbm = panel_rows(a.M, SCORES);
+    const int pbm = panel_rows(a, SCORES);
     a.csplit = panel_csplit(a.M, a.N, a.batch, pbm);
     switch (pbm) {
     case 16: return rag ? launch_kc<SCORES, SCALE, 16, true>(a, stream) : launch_kc<SCORES, SCALE, 16, false>(a, stream);
@@ -543,13 +566,31 @@ bool panel_shape_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, i
 
 bool panel_kernel_applies(const GemmArgs &a, bool trans_b)
 {
-    // Up to 64 rows the skinny kernels stay for narrow outputs, and their generic
-    // tiles for up to 16 rows where N is not whole quads (one head of 16 x 16 x
-    // 128 3.8 us against 5.4; 32 heads of 1 x 3001 x 128 10.7 against 14.3; but
-    // 64 heads of 4 x 16384 x 128 168 against 99, 32 of 50 x 50 x 64 6.9 against 5.1).
-    if (a.M <= 64 && (a.N % 4 == 0 ? a.N < 256 : a.M <= 16)) return false;
     return trans_b && a.vecA && a.vecB &&
            panel_shape_ok(a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.batch, 4);
+}
+
+// The lines below lie where 4000 random products of each kind of 1 to 2048 rows, 4
+// to 16384 columns, 1 to 256 entries and 4 to 128 deep cross over (us on the other
+// kernels -> here).
+bool panel_pays(const GemmArgs &a)
+{
+    const bool whole = whole_quads(a.N, a.C, a.ldc, a.strideC, a.batch);
+    const int64_t steps = panel_steps(a.M, a.N, a.batch);
+    // steps for most CUs, else the direct-B kernel's tiles spread it wider, the more so
+    // the deeper (288 x 247 x 128 13.5 here, 4.3 on them; 115 of 126 x 267 x 128 15.8
+    // here, 22.0; 1 x 82 x 8552 x 12 4.8 here, 9.0)
+    if (a.M > 64)
+        return (a.M >= 256 && whole) || a.K <= 32 || steps * 4 >= device_cus() * (a.K <= 96 ? 1 : 3);
+    // one product: the skinny kernel's strips (9 x 3008 x 128 5.3 here, 3.8 on them),
+    // but at most two chunks deep they are level or behind (7 x 4588 x 28 5.0 -> 3.3)
+    if (a.batch == 1) return a.K <= 64 && (whole || a.M > 32);
+    if (a.K <= 64 || a.M > 32) return true;     // (13 of 60 x 368 x 128 12.6 -> 6.7)
+    // (rows of C in parts: up to 16 rows level, 17 to 32 1.16x faster here until C
+    // fills the memory, 16 of 17 x 5794 x 128 13.1 -> 17.4)
+    if (!whole) return a.M > 16 && steps < 512;
+    // (32 of 2 x 352 x 128 6.7 -> 5.4, 5 of 24 x 4352 x 128 9.7 -> 7.0, 13 of 32 x 384 4.5 -> 5.9)
+    return a.N >= PBN && steps >= (a.M <= 16 ? 64 : 96);
 }
 
 hipError_t launch_gemm_panel(const GemmArgs &g, bool use_alpha, hipStream_t stream)
@@ -574,7 +615,14 @@ hipError_t launch_gemm_panel(const GemmArgs &g, bool use_alpha, hipStream_t stre
 
 bool scores_panel_applies(const OpArgs &a)
 {
-    return a.vecA && a.vecB && panel_shape_ok(a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.batch, 2);
+    if (!a.vecA || !a.vecB || !panel_shape_ok(a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.batch, 2)) return false;
+    const int64_t steps = panel_steps(a.M, a.N, a.batch);
+    // as panel_pays: 17 to 64 rows more than two chunks deep from 40 steps on (2 of
+    // 21 x 64 x 128 4.0 -> 5.0, 11 of 41 x 480 x 128 9.0 -> 5.8), and rows of C that
+    // are not whole quads and shorter than a step from two chunks on, up to 128 of
+    // them (19 of 105 x 18 x 128 7.2 -> 8.1; 32 of 1116 x 74 x 64 12.8 -> 8.9)
+    if (a.M > 16 && a.M <= 64) return a.K <= 64 || steps >= 40;
+    return a.M <= 64 || a.N >= 96 || a.K <= 32 || steps >= 128 || whole_quads(a.N, a.C, a.ldc, a.strideC, a.batch);
 }
 
 hipError_t launch_scores_panel(const OpArgs &o, hipStream_t stream)

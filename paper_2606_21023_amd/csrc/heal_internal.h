@@ -55,14 +55,14 @@ hipError_t launch_gemm_skinny(const GemmArgs &args, bool trans_b, bool use_alpha
                               hipStream_t stream);
 
 // The short-K panel kernel (heal_gemm_panel.hip): B stored N x K, K <= 128,
-// 16-byte rows, at least one panel of rows (256 for bf16x3, 128 for the
-// scores); a panel of A stays in LDS while the workgroup walks the columns
-// of C (attention scores).  HEAL_PANEL 0
-// keeps those products on the tiled kernels.
+// 16-byte rows of A and B, rows of C of any length; a panel of 16 to 256 rows of
+// A stays in LDS while the workgroup walks the columns of C (attention scores).
+// HEAL_PANEL 0 keeps those products on the tiled kernels.
 #ifndef HEAL_PANEL
 #define HEAL_PANEL 1
 #endif
 bool panel_kernel_applies(const GemmArgs &args, bool trans_b);
+bool panel_pays(const GemmArgs &args);   // ... and is the faster kernel for a call it can run
 hipError_t launch_gemm_panel(const GemmArgs &args, bool use_alpha, hipStream_t stream);
 
 hipError_t launch_split(const float *x, uint16_t *hi, uint16_t *lo, int64_t n, hipStream_t stream);

@@ -98,3 +98,36 @@ def test_shallow_products_of_few_rows_keep_the_skinny_kernel(routes):
     assert routes(skinny) == ["skinny"] * len(skinny)
     direct = [(FULL, 64, 8192, 4096), (BASE, 64, 8192, 512), (PRESPLIT, 64, 14336, 4096), (BASE, 64, 65536, 4096)]
     assert all(r.startswith("direct") for r in routes(direct))
+
+
+# attention scores off the large batches (us on the kernel named, on the panel
+# kernel that all of them had been sent to)
+OFF_THE_PANEL = [
+    ((NK, 138, 8608, 128), 11.7, 25.4),      # one panel, 32 workgroups
+    ((NK, 83, 9824, 128, 1, 0, 0, 1), 10.8, 16.0),
+    ((NK, 200, 64, 128), 7.6, 11.7),
+    ((NK, 288, 247, 128), 4.3, 13.5),
+    ((NK, 1, 6720, 128), 3.4, 5.3),
+    ((NK, 10, 288, 128), 3.7, 5.2),
+    ((NK, 22, 11673, 128), 4.9, 6.0),
+    ((NK, 2, 352, 128, 4), 3.7, 5.2),
+    ((NK, 9, 749, 128, 169, 1, 8, 0), 23.3, 30.8),
+    ((I16, 21, 64, 128, 2), 4.0, 5.0),
+    ((I16, 54, 32, 128, 21), 5.1, 5.6),
+    ((I16, 105, 18, 128, 19), 7.2, 8.1),
+]
+# and where it is the faster one (us on the other kernels, on the panel kernel)
+ON_THE_PANEL = [
+    ((NK, 2048, 2048, 128, 32), 0, 0), ((NK, 1531, 1531, 128, 32), 276.8, 130.5),
+    ((NK, 4, 16384, 128, 64), 168, 99), ((NK, 50, 50, 64, 32), 6.9, 5.1),
+    ((NK, 126, 267, 128, 115), 25.9, 15.8), ((NK, 24, 4352, 128, 5), 9.7, 7.0),
+    ((NK, 60, 368, 128, 13), 12.6, 6.7), ((NK, 7, 4588, 28), 5.0, 3.3),
+    ((I16, 1, 3001, 128, 32), 44.6, 8.6), ((I16, 1531, 1531, 128, 32), 172.7, 114.7),
+    ((I16, 4, 16384, 128, 64), 0, 54.9), ((I16, 41, 480, 128, 11), 9.0, 5.8),
+    ((I16, 66, 4868, 96), 7.5, 6.4),
+]
+
+
+def test_scores_take_the_panel_kernel_where_it_is_faster(routes):
+    assert "panel" not in routes([e[0] for e in OFF_THE_PANEL])
+    assert set(routes([e[0] for e in ON_THE_PANEL])) == {"panel"}

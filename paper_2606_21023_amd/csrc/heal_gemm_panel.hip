@@ -555,7 +555,8 @@ bool panel_shape_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, i
 {
     if (K <= 0 || K > PKMAX || (K * es) % 16 != 0 || N < 4) return false;
     const int64_t lim = 0x7fffffffLL;
-    if (((int64_t)255 * lda + K) * es >= lim) return false;
+    const int64_t rows = es == 2 ? 128 : 256;   // of the highest panel
+    if (((M < rows ? M : rows) - 1) * lda * es + K * es >= lim) return false;
     if (((N - 1) * ldb + K) * es >= lim) return false;
     if (((M - 1) * ldc + N) * 4 >= lim) return false;
     // 2^21 16 x 16 blocks at most per launch: the grid stays below 2^31

@@ -75,3 +75,18 @@ def test_quantize_at_the_one_workgroup_limit(orc, n):
     q, m = heal.heal_quantize_i16(to_dev(x))
     qo, mo = orc.quantize_i16(x)
     assert np.array_equal(q.cpu().numpy(), qo) and m.item() == mo
+
+
+def test_rows_of_codes_far_apart():
+    """128 rows 5 000 000 codes apart: the panel's byte offsets reach 1.27 GB."""
+    pitch = 5000000 - 5000000 % 8
+    rng = np.random.default_rng(6)
+    Q, Kt = _codes(rng, (1, 128, 128), 128), _codes(rng, (1, 256, 128), 128)
+    far = torch.zeros((1, 128, pitch), dtype=torch.int16, device="cuda")[:, :, :128]
+    far.copy_(Q)
+    mq, mk = torch.tensor([3.5], device="cuda"), torch.tensor([0.625], device="cuda")
+    announce("scores, rows far apart")
+    S = heal.heal_scores_i16(far, Kt, mq, mk, 0.125)
+    ref = heal.heal_scores_i16(Q, Kt, mq, mk, 0.125)
+    torch.cuda.synchronize()
+    _bits(S, ref, "scores")

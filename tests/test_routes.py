@@ -125,6 +125,8 @@ ON_THE_PANEL = [
     ((I16, 1, 3001, 128, 32), 44.6, 8.6), ((I16, 1531, 1531, 128, 32), 172.7, 114.7),
     ((I16, 4, 16384, 128, 64), 0, 54.9), ((I16, 41, 480, 128, 11), 9.0, 5.8),
     ((I16, 66, 4868, 96), 7.5, 6.4),
+    # codes whose rows lie so far apart that 256 of them pass 2^31 bytes, 128 do not
+    ((I16, 128, 256, 128, 1, 4999872, 0, 0), 0, 0), ((NK, 64, 256, 64, 2, 2499936, 0, 0), 0, 0),
 ]
 
 

@@ -157,19 +157,37 @@ def parse():
     return ap.parse_args()
 
 
-# Rows of the panels of the short-K kernel (heal_gemm_panel.hip) per product.
-PANEL_BM = {"bf16x3": 256, "i16_scores": 128}
-
-
-def panel_applies(method, M, N, K, trans_b):
-    """Whether the library runs the product on the short-K panel kernel: the
-    conditions of panel_kernel_applies / scores_panel_applies for the dense,
-    16-byte aligned operands bench.py allocates (the scores always take B
-    as N x K rows)."""
-    if method not in PANEL_BM or not (trans_b or method == "i16_scores"):
-        return False
-    es = 4 if method == "bf16x3" else 2
-    return 0 < K <= 128 and (K * es) % 16 == 0 and N % 4 == 0 and M >= PANEL_BM[method]
+def panel_rows(method, M, N, K, trans_b, batch, cus=256):
+    """Rows of the panels of the short-K kernel (heal_gemm_panel.hip) where the
+    library runs the product on it, else None: the rules of panel_pays,
+    scores_panel_applies and panel_rows there, for the dense, 16-byte aligned
+    operands bench.py allocates (the scores always take B as N x K rows)."""
+    es = {"bf16x3": 4, "i16_scores": 2}.get(method)
+    if es is None or not (trans_b or method == "i16_scores"):
+        return None
+    if not 0 < K <= 128 or (K * es) % 16 or N < 4:
+        return None
+    steps = batch * (1 if M <= 64 else -(-M // 128)) * -(-N // 128)
+    whole = N % 4 == 0
+    if es == 2:
+        if 16 < M <= 64 and K > 64 and steps < 40:
+            return None
+        if M > 64 and not (N >= 96 or K <= 32 or steps >= 128 or whole):
+            return None
+    elif M > 64:
+        if not (M >= 256 and whole or K <= 32 or 4 * steps >= cus * (1 if K <= 96 else 3)):
+            return None
+    elif batch == 1:
+        if K > 64 or not (whole or M > 32):
+            return None
+    elif K > 64 and M <= 32:
+        if not (N >= 128 and steps >= (64 if M <= 16 else 96) if whole else M > 16 and steps < 512):
+            return None
+    if M <= 64:
+        return 64 if M > 32 else 32 if M > 16 else 16
+    if es == 2 or M <= 128:
+        return 128
+    return 256 if (M <= 256 and steps >= 2048) or (M >= 256 and whole) else 128
 
 
 def direct_tile(method, M, N, K, trans_b, batch):
@@ -177,7 +195,7 @@ def direct_tile(method, M, N, K, trans_b, batch):
     kernel runs it; bench.py's operands are dense and 16-byte aligned."""
     import paper_2606_21023_amd as heal
     kind = {"f16_base": 0, "f16_full": 1, "presplit": 3, "bf16x3": 4}.get(method)
-    if kind is None or panel_applies(method, M, N, K, trans_b):
+    if kind is None or panel_rows(method, M, N, K, trans_b, batch):
         return None
     t = heal.lib().heal_gemm_direct_tile(kind, 1 if trans_b else 0, M, N, K, batch)
     return divmod(t, 1000) if t else None
@@ -617,8 +635,8 @@ def profile_summary(d, out=None):
         f.write(text)
     if traffic is not None:
         inst = {"bf16x3": None, "split": "split"}.get(cfg["method"], "op")
-        if cfg["method"] != "split" and panel_applies(cfg["method"], cfg["M"], cfg["N"], cfg["K"],
-                                                      cfg.get("trans_b", False)):
+        if cfg["method"] != "split" and panel_rows(cfg["method"], cfg["M"], cfg["N"], cfg["K"],
+                                                   cfg.get("trans_b", False), cfg.get("batch", 1)):
             inst = "panel"
         elif direct_tile(cfg["method"], cfg["M"], cfg["N"], cfg["K"], cfg.get("trans_b", False),
                          cfg.get("batch", 1)):
@@ -833,11 +851,13 @@ def main():
     t_mfma = mfma_flops / (BF16_DENSE_PEAK_TFLOPS * 1e12)
     t_hbm = alg_bytes / (HBM_PEAK_GBS * 1e9)
     instance = heal.select_instance(w.M, w.N)
-    if panel_applies(method, w.M, w.N, w.K, w.trans_b):
+    rows = panel_rows(method, w.M, w.N, w.K, w.trans_b, w.batch)
+    if rows:
         key = w.name if method == "bf16x3" else "%s:%s" % (method, w.name)
         traffic = measured_traffic(key, "panel")
         kernel = ("gemm_panel_kernel<%s> (%d-row A panels in LDS, 4 waves of 32 columns, "
-                  "B fragments straight to registers)" % (method, PANEL_BM[method]))
+                  "%s)" % (method, rows, "B read in whole lines and turned through LDS" if rows <= 64
+                             else "B fragments straight to registers"))
     elif direct_tile(method, w.M, w.N, w.K, w.trans_b, w.batch):
         key = w.name if method == "bf16x3" else "%s:%s" % (method, w.name)
         traffic = measured_traffic(key, "direct")

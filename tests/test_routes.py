@@ -133,3 +133,29 @@ ON_THE_PANEL = [
 def test_scores_take_the_panel_kernel_where_it_is_faster(routes):
     assert "panel" not in routes([e[0] for e in OFF_THE_PANEL])
     assert set(routes([e[0] for e in ON_THE_PANEL])) == {"panel"}
+
+
+def test_benchmark_labels_follow_the_choice(routes):
+    """bench.py names the kernel of a product: its copy of the panel kernel's rules,
+    and the library's direct-B tile, against the choice itself."""
+    import random
+    import bench
+    rng = random.Random(17)
+    methods = {"f16_base": BASE, "f16_full": FULL, "i16_scores": I16, "presplit": PRESPLIT}
+    calls, names = [], []
+    for _ in range(4000):
+        method = rng.choice(list(methods) + ["bf16x3"] * 3)
+        M, N = int(2048 ** rng.random()), int(4 * 4096 ** rng.random())
+        K = 8 * rng.randint(1, 16) if rng.random() < 0.7 else 64 * rng.randint(1, 40)
+        trans_b = rng.random() < 0.7
+        batch = rng.choice((1, 3, 32, 100)) if method in ("bf16x3", "i16_scores") else 1
+        calls.append((methods.get(method, NK if trans_b else KN), M, N, K, batch))
+        names.append((method, M, N, K, trans_b, batch))
+    for call, got in zip(names, routes(calls)):
+        tile = bench.direct_tile(*call)
+        if got == "panel":
+            assert bench.panel_rows(*call), call
+        elif got.startswith("direct"):
+            assert tile and "direct %d%03d" % tile == got, call
+        else:
+            assert bench.panel_rows(*call) is None and tile is None, (call, got)

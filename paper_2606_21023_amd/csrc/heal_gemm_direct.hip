@@ -1,6 +1,8 @@
 // The direct-B GEMM kernel for gfx950 (MI355X): products whose output gives a
 // chip of 256 CUs too few large tiles, i.e. most products of more than 64 rows
-// and less than about 2048 x 4096 elements, on operands of any alignment.
+// and less than about 2048 x 4096 elements, those of 17 to 64 rows where the
+// skinny kernels are bound by converting A, and those of few rows whose
+// alignment the 16-byte paths of the other kernels do not take.
 //
 // All products of an FP32 A (HEAL Section 4, GEMM paragraph) run on it:
 // HEAL-Base, HEAL-Full and the pre-split bf16x3 product with their packed B,
@@ -699,6 +701,11 @@ constexpr int kTileN[T_COUNT] = {32, 64, 128, 64, 128, 192, 256, 128, 256, 128, 
 // 7059 x 1141 x 8301 128 x 128 237, 64 x 128 271 us).
 // With an FP32 B, whose raw quads and both parts are held too, they spill
 // (1024 x 4096 K x N: 64 x 256 tiles 179 us, 98 on the tiles it takes now).
+// Of the forms built, these spill: every 128 x 256 one (HEAL-Base 11 registers, 18
+// with a K tail, HEAL-Full 12 and 20, pre-split 44 and 58), the pre-split 96 x 256
+// one with a K tail (10) and the K x N 64 x 64 one with a K tail (4).  The plan's
+// costs were fitted to these times as they are: it takes them where they are
+// faster all the same (2048 x 4096 above).
 
 template <int OP, int BS>
 hipError_t launch_tile(int cfg, const DirectArgs &a, hipStream_t stream)

@@ -17,18 +17,18 @@
 // heads of 1 x 3001 x 128 INT16 44.6 -> 8.6 us, 17.3 with B read in fragment
 // order).
 //
-// The others are bound by writing C: every output element costs 4 bytes
-// of HBM writes against 2K or 4K multiply-adds, so the kernel is built to
-// keep the write stream busy.  A workgroup owns a panel of 128 or 256 rows
-// of A (one batch entry), splits it once into LDS, and then walks its share
+// Panels of 128 and 256 rows are bound by writing C: every output element
+// costs 4 bytes of HBM writes against 2K or 4K multiply-adds, so the kernel is
+// built to keep the write stream busy.  A workgroup owns a panel of A's rows
+// (one batch entry), splits it once into LDS, and then walks its share
 // of the columns of C in steps of 128: each of its four waves loads the B
 // fragments of its 32 columns straight from global memory (B stored N x K:
 // a lane's 8 consecutive k of one column are 32 contiguous bytes), splits
 // them in registers, multiplies them against the whole panel and stores its
 // block of C in whole 128-byte lines, non-temporal (streamed past the
 // caches, which the output would only pollute).  The loads of the next
-// step are issued before the multiplies
-// of the current one, so they have a whole step to arrive, and the stores of
+// step are issued before the multiplies of the current one, so they have a
+// whole step to arrive, and the stores of
 // a step drain while the next one is multiplied.  B goes from L2 to
 // registers once per workgroup (no LDS round trip), and the panel is read
 // from LDS once per 32 columns.
@@ -58,18 +58,12 @@ constexpr int PWN = 32;             // columns per wave and step
 constexpr int PBN = 4 * PWN;        // columns per step
 constexpr uint32_t kOOB = 0x80000000u;  // beyond every buffer range: loads read zeros
 
-// Panel rows (bf16x3, scores), workgroups per panel (each walking half of
-// the columns with 2) and steps of B loads in flight per wave.  Measured on
+// Least workgroups per panel of more than 64 rows (each walking half of the
+// columns with 2) and steps of B loads in flight per wave.  Measured on
 // the attention scores (32 heads, 2048 x 2048 x 128): bf16x3 150 us with
 // 256-row panels against 155 us with 128; the scores 128 us with 128-row
 // panels against 136 us with 256; two workgroups per panel 1.05x faster
 // than one, four slower; two steps of loads in flight slower than one.
-#ifndef HEAL_PANEL_BM
-#define HEAL_PANEL_BM 256
-#endif
-#ifndef HEAL_PANEL_BM_SCORES
-#define HEAL_PANEL_BM_SCORES 128
-#endif
 #ifndef HEAL_PANEL_CSPLIT
 #define HEAL_PANEL_CSPLIT 2
 #endif
@@ -79,7 +73,7 @@ constexpr uint32_t kOOB = 0x80000000u;  // beyond every buffer range: loads read
 #ifndef HEAL_PANEL_PD_SCORES
 #define HEAL_PANEL_PD_SCORES 1
 #endif
-// C stores: with HEAL_PANEL_LINES each store instruction writes whole
+// C stores: each store instruction writes whole
 // 128-byte lines (8 rows x 32 columns, the two 16 x 16 results of a row
 // block traded between lane halves), and HEAL_PANEL_STORE_AUX 2 marks them
 // non-temporal.  Measured on the attention scores: bf16x3 135 us and the
@@ -171,6 +165,8 @@ __device__ __forceinline__ void split8(const u32x4 *raw, u32x4 &h, u32x4 &l)
 // Waves per SIMD: three for the INT16 panels of at most 64 rows, but two for 32
 // rows at full depth, which spilled 11 registers (29 with RAG) under the bound of
 // three (32 heads of 32 x 3001 x 128 18.8 -> 10.8 us, 64 of 17 x 16384 84 -> 56).
+// Three bf16x3 forms at full depth spill a little: 32 rows with RAG 9 registers (with
+// and without SCALE), 128 rows without RAG 2.
 template <bool SCORES, bool SCALE, int KC, int PD, int PBM, bool RAG>
 __global__ void __launch_bounds__(PNT, PBM <= 64   ? (SCORES && !(PBM == 32 && KC == 4) ? 3 : 2)
                                        : PBM <= 128 ? 2 : 1) gemm_panel_kernel(PanelArgs p)
@@ -364,10 +360,9 @@ __global__ void __launch_bounds__(PNT, PBM <= 64   ? (SCORES && !(PBM == 32 && K
         // Row blocks one after another: the panel fragments of block i + 1
         // are read while block i is multiplied, and the block's two 16 x 16
         // results are stored as soon as their chains end, as two stores of
-        // whole 128-byte lines (or, without HEAL_PANEL_LINES, one store of
-        // 16 rows x 64 bytes per result).  The scheduling barriers keep the
-        // compiler from hoisting every LDS read of the step to its top,
-        // which would not fit the registers.
+        // whole 128-byte lines.  The scheduling barriers keep the compiler
+        // from hoisting every LDS read of the step to its top, which would
+        // not fit the registers.
         u32x4 ah[KC], al[KC];
         auto read_a = [&](int i, u32x4 *h, u32x4 *l) {
 #pragma unroll
@@ -537,7 +532,7 @@ hipError_t launch_panel(PanelArgs a, hipStream_t stream)
     case 64: return rag ? launch_kc<SCORES, SCALE, 64, true>(a, stream) : launch_kc<SCORES, SCALE, 64, false>(a, stream);
     case 128: return rag ? launch_kc<SCORES, SCALE, 128, true>(a, stream) : launch_kc<SCORES, SCALE, 128, false>(a, stream);
     case 256:
-        if constexpr (!SCORES || HEAL_PANEL_BM_SCORES == 256)
+        if constexpr (!SCORES)
             return rag ? launch_kc<SCORES, SCALE, 256, true>(a, stream) : launch_kc<SCORES, SCALE, 256, false>(a, stream);
     }
     return hipErrorInvalidValue;

@@ -363,32 +363,6 @@ def bench_split(args, w):
                 "kernel": "split_kernel<true> (8 elements per thread and step)",
                 "per_launch": "8*n bytes (4 read, 2+2 written per element) = %.4g" % alg_bytes,
                 "avg_launch_us": round(ms * 1e3, 2)}
-    # Context for an MFMA-bound product: the vendor library's rate for ONE
-    # plain bf16 GEMM of the same shape on this board (torch.matmul on bf16
-    # copies of the inputs, hipBLASLt), timed after the timed region so that
-    # it cannot change the measured launches.
-    comparison = native()
-    if roofline["bound"] == "mfma" and not batched:
-        Ab = torch.from_numpy(A).to(dev).bfloat16()
-        Bb = torch.from_numpy(B).to(dev).bfloat16()
-        if w.trans_b:                       # B stored N x K
-            Bb = Bb.t().contiguous()
-        for _ in range(10):
-            Ab @ Bb
-        b0, b1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        reps = max(20, min(100, args.steps))
-        b0.record(torch.cuda.current_stream())
-        for _ in range(reps):
-            Ab @ Bb
-        b1.record(torch.cuda.current_stream())
-        torch.cuda.synchronize()
-        ms_bf16 = b0.elapsed_time(b1) / reps
-        tf_bf16 = w.flops / (ms_bf16 * 1e-3) / 1e12
-        comparison.update({"torch_bf16_matmul_tflops": round(tf_bf16, 1),
-                           "torch_bf16_matmul_frac_of_peak": round(tf_bf16 / BF16_DENSE_PEAK_TFLOPS, 4),
-                           "torch_bf16_matmul_ms": round(ms_bf16, 4)})
-        del Ab, Bb
-
     cpu = None
     if not args.no_cpu:
         from oracle import oracle

@@ -142,3 +142,25 @@ def test_strip_width_rule_matches_the_library():
     assert [sw(16032, m) for m in (16, 32, 33, 64)] == [32, 32, 64, 64]
     assert [sw(65536, m) for m in (16, 64)] == [128, 256]
     assert [sw(122625, 16), sw(122624, 16), sw(128256, 64)] == [256, 128, 256]
+
+
+def test_every_global_name_is_defined():
+    """The measuring paths need a GPU to run: their global names at least have
+    to exist (the split's path once used a helper of another function)."""
+    import builtins
+    import dis
+    import types
+
+    def codes(c):
+        yield c
+        for k in c.co_consts:
+            if isinstance(k, types.CodeType):
+                yield from codes(k)
+
+    missing = {(f.__name__, i.argval)
+               for f in vars(bench).values() if isinstance(f, types.FunctionType)
+               and f.__module__ == bench.__name__
+               for c in codes(f.__code__) for i in dis.get_instructions(c)
+               if i.opname == "LOAD_GLOBAL" and not hasattr(bench, i.argval)
+               and not hasattr(builtins, i.argval)}
+    assert not missing

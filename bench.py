@@ -426,6 +426,22 @@ def _kernel_base_name(full):
     return n.split("::")[-1].strip()
 
 
+def traffic_instance(cfg):
+    """Which sources the measured kernel of a JSON line's config comes from."""
+    if cfg["method"] == "split":
+        return "split"
+    call = (cfg["method"], cfg["M"], cfg["N"], cfg["K"], cfg.get("trans_b", False),
+            cfg.get("batch", 1))
+    if panel_rows(*call):
+        return "panel"
+    if direct_tile(*call):
+        return "direct"
+    if cfg["method"] != "bf16x3":
+        return "op"
+    import paper_2606_21023_amd as heal
+    return heal.select_instance(cfg["M"], cfg["N"])
+
+
 def profile_summary(d, out=None):
     """Markdown summary of one rocprofv3 run of this script, from the
     directory DIR it wrote (printed on stdout):
@@ -608,16 +624,7 @@ def profile_summary(d, out=None):
     with open(out, "w") as f:
         f.write(text)
     if traffic is not None:
-        inst = {"bf16x3": None, "split": "split"}.get(cfg["method"], "op")
-        if cfg["method"] != "split" and panel_rows(cfg["method"], cfg["M"], cfg["N"], cfg["K"],
-                                                   cfg.get("trans_b", False), cfg.get("batch", 1)):
-            inst = "panel"
-        elif direct_tile(cfg["method"], cfg["M"], cfg["N"], cfg["K"], cfg.get("trans_b", False),
-                         cfg.get("batch", 1)):
-            inst = "direct"
-        elif inst is None:
-            import paper_2606_21023_amd as heal
-            inst = heal.select_instance(cfg["M"], cfg["N"])
+        inst = traffic_instance(cfg)
         key = cfg["workload"] if cfg["method"] == "bf16x3" else "%s:%s" % (cfg["method"],
                                                                            cfg["workload"])
         t = {"workloads": {}}

@@ -113,6 +113,22 @@ def test_profile_summary_averages_the_timed_dispatches(tmp_path):
     assert "= 1.0000 x 3 products of 2MNK (3.932e+05, exactly)" in text
 
 
+@pytest.mark.parametrize("cfg,inst", [
+    ({"method": "split", "elements": 1 << 20}, "split"),
+    ({"method": "bf16x3", "M": 8192, "N": 8192, "K": 8192}, 1),
+    ({"method": "bf16x3", "M": 16, "N": 4096, "K": 4096}, 3),
+    ({"method": "bf16x3", "M": 256, "N": 256, "K": 256}, "direct"),
+    ({"method": "bf16x3", "M": 2048, "N": 2048, "K": 128, "trans_b": True, "batch": 32}, "panel"),
+    ({"method": "f16_base", "M": 8192, "N": 8192, "K": 8192}, "op"),
+    ({"method": "f16_full", "M": 256, "N": 4096, "K": 4096}, "direct"),
+    ({"method": "i16_scores", "M": 2048, "N": 2048, "K": 128, "batch": 32}, "panel"),
+])
+def test_profile_traffic_is_tied_to_the_measured_kernels_sources(cfg, inst):
+    """The configs of every method's JSON line (the split's has no M, N, K)."""
+    assert bench.traffic_instance(dict(cfg, workload="w")) == inst
+    assert len(bench.kernel_source_hash(inst)) == 16
+
+
 def test_strip_width_rule_matches_the_library():
     """bench.py labels skinny kernels with the strip width the library picks;
     its copy of the rule uses the thresholds heal_gemm_skinny.hip defines."""

@@ -883,6 +883,13 @@ float handicap(float t) { return 1.04f * t + 0.15f; }
 // 40 x 64 x 396 5.5 -> 6.6, HEAL-Base 40 x 192 x 280 4.3 -> 5.0), and so do wide ones
 // less than 2048 deep, bound by C (HEAL-Base 41 x 88568 x 288 15.3 -> 18.4, HEAL-Full
 // 51 x 66444 x 324 17.8 -> 22.0, HEAL-Base 60 x 85184 x 676 27.6 -> 30.2).
+// HEAL-Base and pre-split of 33 to 64 rows stay on the skinny kernels from 15360 to
+// 61440 columns: which tile is the fastest there changes from width to width, with
+// some much slower, and the skinny kernels have no estimate to choose by (64 rows,
+// the same weight again and again, skinny -> the fastest tile, the slowest: HEAL-Base
+// 16032 26.9 -> 24.8, 36.3; 20480 40.7 -> 30.2, 37.4; 32064 48.5 -> 48.1, 58.3; 40960
+// 84.5 -> 67.6, 88.5; 57344 94.8 -> 93.4, 123; pre-split 20480 88.6 -> 73.6, 98.1;
+// 32064 99.7 -> 100, 119).
 bool beats_skinny(int op, bool rows, const DirectArgs &a)
 {
     if (a.batch != 1 || a.K < 512 || a.M <= 16) return false;
